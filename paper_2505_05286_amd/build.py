@@ -24,6 +24,11 @@ SOURCES = [
     "ops.cpp",
     "noalloc.hip",
     "executor.hip",
+    "kernels/gemm_wide_swiglu.hip",
+    "kernels/gemm_wide_bf16.hip",
+    "kernels/gemm_wide_resid.hip",
+    "kernels/gemm_wide_f32.hip",
+    "kernels/gemm_wide_split.hip",
     "kernels/gemm.hip",
     "kernels/norm.hip",
     "kernels/rope_kv.hip",

@@ -83,6 +83,27 @@ __device__ __forceinline__ void dma16_nt(const void* g, void* lds_block) {
   __builtin_amdgcn_global_load_lds((global_ptr_t)g, (lds_ptr_t)lds_block, 16, 0, 2);
 }
 
+// ---- The same DMA and 16-byte loads through a buffer descriptor (MUBUF).  A global_load_lds
+// is a FLAT instruction to the compiler: while one is in flight it can only wait for every
+// LDS read and every load at once.  Buffer accesses are counted exactly, so LDS reads and
+// loads stay in flight across the uses of older ones; their address is a 32-bit lane offset
+// plus a scalar offset (no 64-bit VALU adds), and a lane offset at or past `bytes` reads zeros.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+constexpr int kOutOfRange = (int)0x80000000u;   // a lane offset past every buffer
+
+__device__ __forceinline__ rsrc_t make_rsrc(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+// CACHE: 0, or 2 for the non-temporal hint
+template <int CACHE = 0>
+__device__ __forceinline__ void buf_dma16(rsrc_t r, int lane_off, int scalar_off, void* lds_block) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)lds_block, 16, lane_off, scalar_off, 0, CACHE);
+}
+template <int CACHE = 0>
+__device__ __forceinline__ uint4 buf_load16(rsrc_t r, int lane_off, int scalar_off) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, scalar_off, CACHE));
+}
+
 // s_waitcnt vmcnt(N) with the other counters left alone (gfx9 encoding)
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {

@@ -4,27 +4,20 @@
 // the packed weights (see below).  Three kernels (gemm_plan picks):
 //   gemm_stream_kernel: weight streaming through LDS DMA on 16x16x32 MFMAs, split K;
 //     M <= 128;
-//   gemm_big_kernel: macro tiles of up to 256 x 256 on 32x32x16 MFMAs fed by LDS DMA,
-//     four or eight wavefronts, tile shape chosen per GEMM; M > 512, outputs of
-//     N >= 16384 above 64 rows, SwiGLU above 128 rows, and 128 < M <= 512 with split
-//     K otherwise;
+//   gemm_wide_kernel (gemm_wide.hpp): tiles of 64-256 rows x 256 columns, the weights
+//     straight to registers; M > 128, and outputs of N >= 16384 above 64 rows;
 //   gemm_nt_kernel: 128x128 tiles of 16x16x32 MFMAs, K staged through LDS from
-//     registers; SwiGLU whose N is not a multiple of 64 on the big kernel's shapes.
+//     registers; SwiGLU whose N is not a multiple of 64 on the wide kernel's shapes.
 // Workgroups are renumbered so that consecutive output tiles (which share a
 // weight slice) land on the same XCD and its L2.
-#include <hip/hip_ext.h>
-
 #include <algorithm>
 #include <utility>
 
-#include "common.hpp"
-#include "kernels.hpp"
+#include "gemm_util.hpp"
 
 namespace hxf {
 
 namespace {
-
-constexpr int BK_MAX = 128;
 
 // B operands are packed weights: 16-row x 32-column tiles of 1 KB, row-tiles
 // outermost, and inside a tile the 8-element chunks in MFMA operand order
@@ -51,27 +44,12 @@ __device__ __forceinline__ uint4 load16(const bf16_t* p) {
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-__device__ __forceinline__ int xcd_remap(int i, int nb) {
-  const int xcd = i & 7, local = i >> 3;
-  const int per = nb >> 3, rem = nb & 7;
-  return (xcd < rem) ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
-}
-
-// Launch; with events, the kernel itself records its start (e0) and end (e1).
-template <typename K, typename... Args>
-hipError_t launch_ev(K kernel, dim3 grid, dim3 block, hipStream_t st, hipEvent_t e0, hipEvent_t e1, Args... args) {
-  if (e0 || e1) hipExtLaunchKernelGGL(kernel, grid, block, 0, st, e0, e1, 0, args...);
-  else hipLaunchKernelGGL(kernel, grid, block, 0, st, args...);
-  return hipGetLastError();
-}
-
-template <int BM, int BN, int BK, int NS, int EPI, bool SPLIT>
+template <int BM, int BN, int BK, int NS>
 __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs a) {
   constexpr int LDS_ROW = BK + 8;                   // bf16 elements per LDS row (16-byte pad)
   constexpr int TM = BM / 32, TN = BN / 32;         // MFMA tiles per wave
   constexpr int A_CH = BM * (BK / 8) / 256;         // 16-byte chunks per thread
   constexpr int B_CH = BN * (BK / 8) / 256;
-  constexpr bool SW = (EPI == EPI_SWIGLU);
   __shared__ __attribute__((aligned(16))) bf16_t As[BM * LDS_ROW];
   __shared__ __attribute__((aligned(16))) bf16_t Bs[BN * LDS_ROW];
 
@@ -80,8 +58,7 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs a) {
   const int L = xcd_remap(blockIdx.x, tiles_m * tiles_n);
   const int tn = L / tiles_m, tm = L % tiles_m;
   const int m0 = tm * BM, n0 = tn * BN;
-  const int kb = SPLIT ? blockIdx.z * a.k_chunk : 0;
-  const int ke = SPLIT ? min(a.K, kb + a.k_chunk) : a.K;
+  const int ke = a.K;
 
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int wm = wid >> 1, wn = wid & 1;
@@ -102,7 +79,7 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs a) {
   for (int j = 0; j < B_CH; ++j) {
     const int r = (tid + j * 256) / CPR;
     b_ok[j] = (n0 + r) < a.N;
-    b_ptr[j] = b_row(a, b_ok[j] ? n0 + r : 0, SW) + b_koff(c16 * 8);
+    b_ptr[j] = b_row(a, b_ok[j] ? n0 + r : 0, true) + b_koff(c16 * 8);
   }
   // NS register stages: the K tiles it+1 .. it+NS-1 are in flight while tile it
   // is multiplied (one stage is the tile being stored to LDS).
@@ -159,8 +136,8 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs a) {
 
 #pragma unroll
   for (int st = 0; st < NS; ++st)
-    if (kb + st * BK < ke) fetch(ra[st], rb[st], kb + st * BK);
-  for (int k0 = kb; k0 < ke; k0 += NS * BK) {
+    if (st * BK < ke) fetch(ra[st], rb[st], st * BK);
+  for (int k0 = 0; k0 < ke; k0 += NS * BK) {
 #pragma unroll
     for (int st = 0; st < NS; ++st) {
       const int kt = k0 + st * BK;
@@ -176,56 +153,21 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs a) {
 
   // epilogue: lane holds rows (lane/16)*4 + e, column lane%16 of each 16x16 tile
   const int col_in = lane & 15, row_q = (lane >> 4) * 4;
-  if (SPLIT) {
-    float* P = a.partial + (size_t)blockIdx.z * a.M * a.N;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int col = n0 + wn * (BN / 2) + j * 16 + col_in;
-        if (col >= a.N) continue;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int row = m0 + wm * (BM / 2) + i * 16 + row_q + e;
-          if (row < a.M) P[(size_t)row * a.N + col] = acc[i][j][e];
-        }
-      }
-    return;
-  }
-  if (EPI == EPI_SWIGLU) {
-    bf16_t* C = reinterpret_cast<bf16_t*>(a.C);
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; j += 2) {
-        const int lc = n0 + wn * (BN / 2) + j * 16;          // first (gate) logical column of the pair
-        if (lc >= a.N) continue;
-        const int col = (lc >> 5) * 16 + col_in;              // output column
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int row = m0 + wm * (BM / 2) + i * 16 + row_q + e;
-          if (row < a.M) {
-            const float g = acc[i][j][e], u = acc[i][j + 1][e];
-            C[(size_t)row * a.ldc + col] = f2bf(g / (1.f + __expf(-g)) * u);
-          }
-        }
-      }
-    return;
-  }
+  bf16_t* C = reinterpret_cast<bf16_t*>(a.C);
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int col = n0 + wn * (BN / 2) + j * 16 + col_in;
-      if (col >= a.N) continue;
+    for (int j = 0; j < TN; j += 2) {
+      const int lc = n0 + wn * (BN / 2) + j * 16;          // first (gate) logical column of the pair
+      if (lc >= a.N) continue;
+      const int col = (lc >> 5) * 16 + col_in;              // output column
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int row = m0 + wm * (BM / 2) + i * 16 + row_q + e;
-        if (row >= a.M) continue;
-        const size_t o = (size_t)row * a.ldc + col;
-        if (EPI == EPI_BF16) reinterpret_cast<bf16_t*>(a.C)[o] = f2bf(acc[i][j][e]);
-        else if (EPI == EPI_RESID) reinterpret_cast<float*>(a.C)[o] += acc[i][j][e];
-        else reinterpret_cast<float*>(a.C)[o] = acc[i][j][e];
+        if (row < a.M) {
+          const float g = acc[i][j][e], u = acc[i][j + 1][e];
+          C[(size_t)row * a.ldc + col] = f2bf(g / (1.f + __expf(-g)) * u);
+        }
       }
     }
 }
@@ -447,299 +389,6 @@ hipError_t launch_stream(const GemmArgs& a, int S, hipStream_t st, bool reduce, 
   return launch_ev(gemm_stream_kernel<MT, EPI, false>, dim3(nb, 1), dim3(64 * ST_WV), st, e0, e1, a);
 }
 
-// Prefill-sized M: BM x BN macro tiles on the 32x32x16 bf16 MFMA, fed by the
-// LDS DMA path.  A stage is 32 of K: the BM/16 A blocks (16 rows x 32 columns
-// of the activations, 1 KB each, in the MFMA operand order [k/8][row][8]) and
-// the BN/16 packed weight tiles, DMA'd by the WM x WN wavefronts together (each
-// moves the same number of blocks; where the blocks do not divide evenly the
-// last block is moved again, an identical write); NSTG stages in flight in
-// distinct LDS arrays (see the streaming kernel for the wait and barrier
-// discipline).  Wavefront (wm, wn) owns rows wm*BM/WM.. and columns wn*BN/WN..
-// as tiles of 32 x 32.  With eight wavefronts two share each SIMD, so one issues
-// MFMAs while the other waits on LDS.  BM is any multiple of 32 so that the
-// row tiles can match the batch (2080 rows = 13 x 160).  SwiGLU groups logical
-// columns by 64 (32 gate rows, then the 32 matching up rows) so one lane holds
-// both; it needs BN/WN a multiple of 64.  SPLIT: grid.y splits K into chunks of
-// k_chunk (a multiple of 32) and each writes its fp32 partial [M][N] to slot
-// blockIdx.y of a.partial, summed by the consumer (not with SwiGLU).
-template <int BM, int BN, int WM, int WN, int NSTG, int EPI, bool SPLIT>
-__global__ __launch_bounds__(64 * WM * WN, 1) void gemm_big_kernel(GemmArgs a) {
-  constexpr int W = WM * WN;
-  constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
-  static_assert(TM * WM * 32 == BM && TN * WN * 32 == BN, "wavefront tiling");
-  constexpr int AB = BM / 16, BB = BN / 16, NBLK = AB + BB;   // 1 KB blocks per stage
-  constexpr int PER_W = (NBLK + W - 1) / W;                   // DMA instructions per wavefront per stage
-  constexpr int STAGE = NBLK * 512;
-  constexpr bool SW = (EPI == EPI_SWIGLU);
-  static_assert(!SW || TN % 2 == 0, "SwiGLU pairs 32-column tiles");
-  static_assert(!(SW && SPLIT), "split partials hold logical columns; SwiGLU needs both halves summed first");
-  static_assert(NSTG >= 3 && NSTG <= 5 && NSTG * STAGE * 2 <= 160 * 1024, "stage layout");
-  __shared__ __attribute__((aligned(1024))) bf16_t L0[STAGE], L1[STAGE], L2[STAGE], L3[NSTG > 3 ? STAGE : 8],
-      L4[NSTG > 4 ? STAGE : 8];
-  auto slot = [&](auto ic) -> bf16_t* {
-    constexpr int I = decltype(ic)::value;
-    if constexpr (I == 0) return L0; else if constexpr (I == 1) return L1; else if constexpr (I == 2) return L2;
-    else if constexpr (I == 3) return L3; else return L4;
-  };
-  const int tiles_m = (a.M + BM - 1) / BM;
-  const int tiles_n = (a.N + BN - 1) / BN;
-  const int L = xcd_remap(blockIdx.x, tiles_m * tiles_n);
-  const int tn = L / tiles_m, tm = L % tiles_m;
-  const int m0 = tm * BM, n0 = tn * BN;
-  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = w / WN, wn = w % WN;
-  const int kb = SPLIT ? blockIdx.y * a.k_chunk : 0;
-  const int ke = SPLIT ? min(a.K, kb + a.k_chunk) : a.K;
-  const int nst = (ke - kb + 31) / 32;
-
-  // This wavefront's DMA blocks w*PER_W + u: an A block (16 activation rows, the
-  // lane's row and 8-column chunk; with packed activations a 1 KB tile like the
-  // weights') or a packed weight tile (1 KB contiguous).  No per-block branches at
-  // issue time, so the compiler keeps track of which LDS array each DMA writes.
-  const bf16_t* src[PER_W];
-  int step[PER_W];   // elements per stage: 32 along an activation row, 512 for a weight tile
-  int dst[PER_W];
-#pragma unroll
-  for (int u = 0; u < PER_W; ++u) {
-    const int gb = min(w * PER_W + u, NBLK - 1);
-    dst[u] = gb * 512;
-    if (gb < AB && a.a_packed) {
-      // row tiles past M repeat the last one (its rows past M are never stored)
-      src[u] = a.A + (size_t)min(m0 / 16 + gb, (a.M - 1) / 16) * a.kt * 512 + lane * 8;
-      step[u] = 512;
-    } else if (gb < AB) {
-      src[u] = a.A + (size_t)min(m0 + gb * 16 + (lane & 15), a.M - 1) * a.lda + (lane >> 4) * 8;
-      step[u] = 32;
-    } else {
-      const int c = min(n0 + (gb - AB) * 16, a.N - 1) & ~15;   // logical column of the tile (past N: repeat)
-      const bf16_t* mat = a.B;
-      int row = c;
-      if (SW) {
-        const int g = c >> 6, w64 = c & 63;
-        mat = (w64 < 32) ? a.B : a.B2;
-        row = g * 32 + (w64 & 31);
-      }
-      src[u] = mat + (size_t)(row >> 4) * a.kt * 512 + lane * 8;
-      step[u] = 512;
-    }
-  }
-  // A past K: a chunk of the row is read again (its weights are zero): the lane's last
-  // in-row chunk, or the row's first when K < 32 (never an address before the row)
-  const int a_last = max(a.K - 8 - (lane >> 4) * 8, 0);
-  auto issue = [&](int s, bf16_t* base) {
-    const int k0 = kb + min(s, nst - 1) * 32;   // past the end: reload the last stage (unused)
-#pragma unroll
-    for (int u = 0; u < PER_W; ++u) {
-      const int off = step[u] == 32 ? min(k0, a_last) : (k0 >> 5) * 512;
-      dma16(src[u] + off, base + dst[u]);
-    }
-  };
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  // 32x32x16 operand of lane l: row (or column) l % 32 of the tile, k chunk l / 32 of the
-  // 16-wide slice.  The offsets are precomputed so that every LDS read is its array plus
-  // one offset: the compiler must still see which array a read comes from, or it waits
-  // for every DMA in flight.
-  const int lo = ((lane & 31) >> 4) * 512 + (lane >> 5) * 128 + (lane & 15) * 8;
-  int a_off[TM], b_off[TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i) a_off[i] = ((wm * TM + i) * 2) * 512 + lo;
-#pragma unroll
-  for (int j = 0; j < TN; ++j) b_off[j] = (AB + (wn * TN + j) * 2) * 512 + lo;
-  // all fragments of a stage are read first (distinct registers), then the MFMAs; the
-  // scheduling groups interleave one LDS read with one MFMA so that the reads' latency
-  // hides under the matrix pipe instead of stalling it
-  auto compute = [&](const bf16_t* base) {
-    bf16x8 fa[2][TM], fb[2][TN];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-#pragma unroll
-      for (int j = 0; j < TN; ++j) fb[q][j] = as_bf16x8(*reinterpret_cast<const uint4*>(base + b_off[j] + q * 256));
-#pragma unroll
-      for (int i = 0; i < TM; ++i) fa[q][i] = as_bf16x8(*reinterpret_cast<const uint4*>(base + a_off[i] + q * 256));
-    }
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = mfma32x32x16(fa[q][i], fb[q][j], acc[i][j]);
-    constexpr int RD = 2 * (TM + TN), MF = 2 * TM * TN, PAIRS = RD < MF ? RD : MF;
-    static_for<PAIRS>([&](auto) {
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-    });
-    if constexpr (MF > PAIRS) __builtin_amdgcn_sched_group_barrier(0x008, MF - PAIRS, 0);
-    if constexpr (RD > PAIRS) __builtin_amdgcn_sched_group_barrier(0x100, RD - PAIRS, 0);
-  };
-
-  static_for<NSTG - 1>([&](auto ic) { issue(decltype(ic)::value, slot(ic)); });
-  int s0 = 0;
-  for (; s0 + NSTG <= nst; s0 += NSTG) {
-    static_for<NSTG>([&](auto ic) {
-      constexpr int J = decltype(ic)::value;
-      wait_vmcnt<(NSTG - 2) * PER_W>();
-      __builtin_amdgcn_s_barrier();
-      issue(s0 + J + NSTG - 1, slot(std::integral_constant<int, (J + NSTG - 1) % NSTG>{}));
-      compute(slot(ic));
-    });
-  }
-  wait_vmcnt<0>();
-  __builtin_amdgcn_s_barrier();
-  static_for<NSTG - 1>([&](auto ic) {
-    if (s0 + decltype(ic)::value < nst) compute(slot(ic));
-  });
-
-  // lane holds column l % 32 and rows 8*(r/4) + 4*(lane/32) + r%4 of each 32x32 tile
-  const int l32 = lane & 31, rq = (lane >> 5) * 4;
-  const int wr0 = m0 + wm * (BM / WM), wc0 = n0 + wn * (BN / WN);
-  if (SPLIT) {
-    float* P = a.partial + (size_t)blockIdx.y * a.M * a.N;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = wr0 + i * 32 + (r >> 2) * 8 + rq + (r & 3);
-        if (row >= a.M) continue;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int col = wc0 + j * 32 + l32;
-          if (col < a.N) P[(size_t)row * a.N + col] = acc[i][j][r];
-        }
-      }
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    if (EPI == EPI_RESID) {
-      // residual loads of RB rows first, then the adds and stores (one wait per RB rows)
-      constexpr int RB = TN > 3 ? 4 : TN > 1 ? 8 : 16;
-      float* C = reinterpret_cast<float*>(a.C);
-#pragma unroll
-      for (int r0 = 0; r0 < 16; r0 += RB) {
-        float old[RB][TN];
-#pragma unroll
-        for (int r = 0; r < RB; ++r) {
-          const int rr = r0 + r;
-          const int row = min(wr0 + i * 32 + (rr >> 2) * 8 + rq + (rr & 3), a.M - 1);
-#pragma unroll
-          for (int j = 0; j < TN; ++j) old[r][j] = C[(size_t)row * a.ldc + min(wc0 + j * 32 + l32, a.N - 1)];
-        }
-#pragma unroll
-        for (int r = 0; r < RB; ++r) {
-          const int rr = r0 + r;
-          const int row = wr0 + i * 32 + (rr >> 2) * 8 + rq + (rr & 3);
-          if (row >= a.M) continue;
-#pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            const int col = wc0 + j * 32 + l32;
-            if (col < a.N) C[(size_t)row * a.ldc + col] = old[r][j] + acc[i][j][rr];
-          }
-        }
-      }
-      continue;
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = wr0 + i * 32 + (r >> 2) * 8 + rq + (r & 3);
-      if (row >= a.M) continue;
-      if (SW) {
-#pragma unroll
-        for (int j = 0; j < TN; j += 2) {
-          const int lc = wc0 + j * 32;   // first (gate) logical column of the 64-group
-          if (lc >= a.N) continue;
-          const float g = acc[i][j][r], u = acc[i][j + 1][r];
-          const int oc = (lc >> 6) * 32 + l32;
-          reinterpret_cast<bf16_t*>(a.C)[a.c_kt ? packed_elem(row, oc, a.c_kt) : (size_t)row * a.ldc + oc] =
-              f2bf(g / (1.f + __expf(-g)) * u);
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int col = wc0 + j * 32 + l32;
-          if (col >= a.N) continue;
-          const size_t o = (size_t)row * a.ldc + col;
-          if (EPI == EPI_BF16) reinterpret_cast<bf16_t*>(a.C)[o] = f2bf(acc[i][j][r]);
-          else reinterpret_cast<float*>(a.C)[o] = acc[i][j][r];
-        }
-      }
-    }
-  }
-}
-
-// Macro-tile shapes of the big kernel: (BM, BN, WM x WN wavefronts), a per-flop cost
-// factor measured on the projection shapes (smaller tiles move more bytes per flop,
-// one-row wavefront grids read more LDS per MFMA), and whether the wavefront column
-// span suits SwiGLU.  Stages: as many as fit 160 KB of LDS, at most five.
-struct BigCfg {
-  int bm, bn, wm, wn;
-  double f;
-  bool swiglu;
-};
-constexpr BigCfg kBig[] = {
-    {256, 256, 4, 2, 1.02, true}, {224, 256, 1, 8, 1.10, false}, {192, 256, 2, 4, 1.0, true},
-    {160, 256, 1, 8, 1.17, false}, {128, 256, 2, 4, 1.3, true},    {128, 128, 2, 2, 1.6, true},
-    {256, 128, 2, 2, 1.3, true},
-};
-constexpr int kNumBig = sizeof(kBig) / sizeof(kBig[0]);
-constexpr int kNumPrefillBig = 6;   // the shapes chosen among for M > 512
-
-template <int BM, int BN, int WM, int WN, int EPI>
-hipError_t launch_big(const GemmArgs& a, int S, hipStream_t st, bool reduce, hipEvent_t e0, hipEvent_t e1) {
-  constexpr int STAGE_BYTES = (BM + BN) * 64;
-  constexpr int NSTG = std::min(5, 160 * 1024 / STAGE_BYTES);
-  const int nb = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  if constexpr (EPI != EPI_SWIGLU) {
-    if (S > 1) {
-      if (hipError_t e = launch_ev(gemm_big_kernel<BM, BN, WM, WN, NSTG, EPI, true>, dim3(nb, S), dim3(64 * WM * WN),
-                                   st, e0, reduce ? nullptr : e1, a))
-        return e;
-      if (!reduce) return hipSuccess;
-      const size_t tot = (size_t)a.M * a.N;
-      return launch_ev(splitk_reduce_kernel<EPI>, dim3((tot + 255) / 256), dim3(256), st, nullptr, e1, a, S);
-    }
-  } else {
-    if (S > 1) return hipErrorInvalidValue;
-  }
-  return launch_ev(gemm_big_kernel<BM, BN, WM, WN, NSTG, EPI, false>, dim3(nb), dim3(64 * WM * WN), st, e0, e1, a);
-}
-
-template <int EPI>
-hipError_t launch_big_cfg(const GemmArgs& a, int cfg, int S, hipStream_t st, bool reduce, hipEvent_t e0,
-                          hipEvent_t e1) {
-  switch (cfg) {
-    case 0: return launch_big<256, 256, 4, 2, EPI>(a, S, st, reduce, e0, e1);
-    case 2: return launch_big<192, 256, 2, 4, EPI>(a, S, st, reduce, e0, e1);
-    case 4: return launch_big<128, 256, 2, 4, EPI>(a, S, st, reduce, e0, e1);
-    case 5: return launch_big<128, 128, 2, 2, EPI>(a, S, st, reduce, e0, e1);
-    case 6: return launch_big<256, 128, 2, 2, EPI>(a, S, st, reduce, e0, e1);
-    default: break;
-  }
-  if constexpr (EPI != EPI_SWIGLU) {
-    if (cfg == 1) return launch_big<224, 256, 1, 8, EPI>(a, S, st, reduce, e0, e1);
-    if (cfg == 3) return launch_big<160, 256, 1, 8, EPI>(a, S, st, reduce, e0, e1);
-  }
-  return hipErrorInvalidValue;
-}
-
-template <int BM, int BN, int BK, int NS, int EPI>
-hipError_t launch_tile(const GemmArgs& a, int S, hipStream_t st, bool reduce, hipEvent_t e0, hipEvent_t e1) {
-  const int nb = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  if (S <= 1) return launch_ev(gemm_nt_kernel<BM, BN, BK, NS, EPI, false>, dim3(nb), dim3(256), st, e0, e1, a);
-  if (hipError_t e = launch_ev(gemm_nt_kernel<BM, BN, BK, NS, EPI, true>, dim3(nb, 1, S), dim3(256), st, e0,
-                               reduce ? nullptr : e1, a))
-    return e;
-  if (!reduce) return hipSuccess;
-  const int n_out = (EPI == EPI_SWIGLU) ? a.N / 2 : a.N;
-  const size_t tot = (size_t)a.M * n_out;
-  return launch_ev(splitk_reduce_kernel<EPI>, dim3((tot + 255) / 256), dim3(256), st, nullptr, e1, a, S);
-}
-
 template <int EPI>
 hipError_t launch_epi(GemmArgs a, const GemmPlan& p, hipStream_t st, bool reduce, hipEvent_t e0, hipEvent_t e1) {
   a.k_chunk = p.k_chunk;
@@ -748,12 +397,24 @@ hipError_t launch_epi(GemmArgs a, const GemmPlan& p, hipStream_t st, bool reduce
     if (p.bm <= 64) return launch_stream<4, EPI>(a, p.splits, st, reduce, e0, e1);
     return launch_stream<8, EPI>(a, p.splits, st, reduce, e0, e1);
   }
-  if (p.big) {
-    // SwiGLU on the big kernel pairs 32 gate with 32 up columns: needs F % 32 == 0
-    if (EPI == EPI_SWIGLU && a.N % 64 != 0) return launch_tile<128, 128, 64, 2, EPI>(a, 1, st, true, e0, e1);
-    return launch_big_cfg<EPI>(a, p.cfg, p.splits, st, reduce, e0, e1);
+  // (SwiGLU on the wide kernel pairs 32 gate with 32 up columns: F % 32 == 0)
+  if (p.wide && !(EPI == EPI_SWIGLU && a.N % 64 != 0)) {
+    if (p.splits > 1) {
+      if (hipError_t e = gemm_wide_split(a, p, st, e0, reduce ? nullptr : e1)) return e;
+      if (!reduce) return hipSuccess;
+      const size_t tot = (size_t)a.M * a.N;
+      return launch_ev(splitk_reduce_kernel<EPI>, dim3((tot + 255) / 256), dim3(256), st, nullptr, e1, a, p.splits);
+    }
+    if constexpr (EPI == EPI_BF16) return gemm_wide_bf16(a, p, st, e0, e1);
+    if constexpr (EPI == EPI_RESID) return gemm_wide_resid(a, p, st, e0, e1);
+    if constexpr (EPI == EPI_SWIGLU) return gemm_wide_swiglu(a, p, st, e0, e1);
+    return gemm_wide_f32(a, p, st, e0, e1);
   }
-  return launch_tile<128, 128, 64, 2, EPI>(a, p.splits, st, reduce, e0, e1);
+  if constexpr (EPI == EPI_SWIGLU) {
+    const int nb = ((a.M + 127) / 128) * ((a.N + 127) / 128);
+    return launch_ev(gemm_nt_kernel<128, 128, 64, 2>, dim3(nb), dim3(256), st, e0, e1, a);
+  }
+  return hipErrorInvalidValue;
 }
 
 // One 16-byte chunk of the packed layout per thread: chunk q is tile q / 64 and,
@@ -782,80 +443,70 @@ hipError_t pack_weight_launch(const uint16_t* W, int N, int K, uint16_t* out, hi
   return hipGetLastError();
 }
 
-// Kernel, tile and split-K choice.  M <= 128: the weight-streaming kernel, except
-// for wide outputs (N >= 16384) above 64 rows, which take the big-tile kernel as
-// every M > 512 and every SwiGLU above 128 rows do.  The other 128 < M <= 512
-// shapes: the big-tile kernel with split K.
+// Estimated time (us) of the wide kernel with 16 tm x 64 wv tiles and K cut into pieces of
+// k_chunk.  Fitted to 6,800 measured launches (12 projection shapes of d 4096-8192, 65-2300
+// rows, every tile height and split; weights not in the caches; 8% rms error): a step of 32 of
+// K takes the longest of the matrix pipe's issue time, its power-limited time (which grows
+// with the CUs at work) and the time one CU needs to fetch its weights; workgroups run in
+// rounds of one per CU; the weights come at 5.4 TB/s at best; fp32 partials cost 0.25 us per MB
+// written and 0.2 read back.
+static double wide_time(int M, int N, int K, int tm, int wv, int k_chunk) {
+  const int tiles_m = (M + 16 * tm - 1) / (16 * tm), tiles_n = (N + 64 * wv - 1) / (64 * wv);
+  const int splits = (K + k_chunk - 1) / k_chunk;
+  const int wgs = tiles_m * tiles_n * splits;
+  const double eff = (wv == 8 ? 1.87 : 1.0) * (tm == 16 ? 1.05 : 1.0);
+  const double steps = k_chunk / 32.0, fetch = tiles_m == 1 ? 0.39 : tiles_m < 4 ? 0.35 : 0.31;
+  auto round = [&](int n) {
+    return steps * std::max({(0.14 + 0.0297 * tm) * eff, (0.1106 + 0.041 * tm) * eff * n / 256.0, fetch}) + 0.4;
+  };
+  double t = wgs / 256 * round(256) + (wgs % 256 ? round(wgs % 256) : 0.0);
+  t = std::max(t, (double)N * K * 2e-6 / 5.4);
+  return t + (splits > 1 ? 0.45e-6 * splits * ((M + 15) / 16 * 16) * (double)N * 4 : 0.0);
+}
+
+// Kernel, tile and split-K choice.  M <= 128: the weight-streaming kernel, except for wide
+// outputs (N >= 16384) above 64 rows, which take the wide kernel as every larger M does.  Up
+// to 512 rows its K may be split (the partials of more rows cost more than the split gains);
+// neither for wide outputs, which fill the chip, nor for SwiGLU.  Partials outgrow the array of
+// the allocation-free entry point only where they buy much (a million outputs or more, pieces
+// of 2048 of K), so that the shapes it serves do not hang on small gains.  Tile and split
+// minimise the estimate above, and depend on M only through its 16-row tiles.
 GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu) {
   GemmPlan p;
-  // big tiles: the shape minimising whole rounds of one workgroup per CU times tile area
-  // times its cost factor (the last round costs as much as a full one)
-  auto big = [&]() {
+  if (M > 128 || (M > 64 && N >= 16384)) {
+    p.wide = true;
+    const int most = M <= 512 && N < 16384 && !swiglu ? max_splits : 1;
     double best = 0;
-    for (int c = 0; c < kNumPrefillBig; ++c) {
-      const BigCfg& g = kBig[c];
-      if (swiglu && !g.swiglu) continue;
-      const int tiles = ((M + g.bm - 1) / g.bm) * ((N + g.bn - 1) / g.bn);
-      const double cost = (double)((tiles + 255) / 256) * g.bm * g.bn * g.f;
-      if (best == 0 || cost < best - 1e-6) {
-        best = cost;
-        p.cfg = c;
-        p.bm = g.bm;
-        p.bn = g.bn;
-      }
-    }
-    p.big = true;
-    p.splits = 1;
-    p.k_chunk = K;
-    return p;
-  };
-  // 128 < M <= 512, N < 16384, not SwiGLU: big tiles with K split (fp32 partials the
-  // consumer sums).  Shape and split minimise a per-launch estimate fitted to measured
-  // times on the 8B projections at 128-512 rows: 0.366 us per million tile-area x
-  // K-chunk x cost-factor units (every workgroup of a round runs at once), plus 0.24 us
-  // per MB of partials written and read back.
-  auto mid = [&]() {
-    double best = 0;
-    for (int c : {4, 5, 0, 6}) {
-      const BigCfg& g = kBig[c];
-      const int tiles = ((M + g.bm - 1) / g.bm) * ((N + g.bn - 1) / g.bn);
-      for (int s = 1; s <= max_splits; ++s) {
-        if (s > 1 && (tiles * s > 256 || K / s < 512)) break;
-        const int kc = ((K + s - 1) / s + 31) / 32 * 32;
-        const int splits = (K + kc - 1) / kc;
-        const double rounds = (tiles * splits + 255) / 256;
-        const double t = 0.366e-6 * rounds * g.bm * g.bn * (double)kc * g.f +
-                         (splits > 1 ? 0.24e-6 * splits * (double)M * N * 4 : 0.0);
-        if (best == 0 || t < best - 1e-9) {
-          best = t;
-          p.cfg = c;
-          p.bm = g.bm;
-          p.bn = g.bn;
-          p.k_chunk = kc;
-          p.splits = splits;
-        }
-      }
-    }
-    p.big = true;
-    return p;
-  };
-  if (M > 128 && M <= 512 && N < 16384 && !swiglu) return mid();
-  if (M > 512 || (M > 64 && N >= 16384) || (M > 128 && swiglu)) return big();
-  if (M <= 128) {
-    // weight streaming (16 * MT rows): 128 columns per workgroup; K split into the most
-    // pieces that keep the grid within one workgroup per CU and >= 512 of K per piece
-    p.stream = true;
-    p.bm = M <= 32 ? 32 : M <= 64 ? 64 : 128;
-    const int tiles = (N + ST_COLS - 1) / ST_COLS;
-    int s = 1;
-    while (s + 1 <= max_splits && tiles * (s + 1) <= 256 && K / (s + 1) >= 512) ++s;
-    p.k_chunk = (((K + s - 1) / s) + ST_KS - 1) / ST_KS * ST_KS;
-    p.splits = (K + p.k_chunk - 1) / p.k_chunk;
+    auto consider = [&](int tm, int wv, int s) {
+      const int kc = ((K + s - 1) / s + 63) / 64 * 64;
+      const double t = wide_time(M, N, K, tm, wv, kc);
+      if (best != 0 && t >= best) return;
+      best = t;
+      p.tm = tm;
+      p.wv = wv;
+      p.bm = 16 * tm;
+      p.bn = 64 * wv;
+      p.k_chunk = kc;
+      p.splits = (K + kc - 1) / kc;
+    };
+    const int row_tiles = (M + 15) / 16;
+    for (int tm = 4; tm <= std::min(16, std::max(4, row_tiles)); ++tm)
+      for (int s = 1; s <= most && (s == 1 || K / s >= 512); ++s)
+        if (s == 1 || (K / s >= 2048 && (int64_t)M * N >= 1 << 20) ||
+            (int64_t)s * row_tiles * 16 * N * 4 <= kNoallocPartials)
+          consider(tm, 4, s);
+    if (M > 512) consider(9, 8, 1);
     return p;
   }
-  p.bm = 128;
-  p.splits = 1;
-  p.k_chunk = K;
+  // weight streaming (16 * MT rows): 128 columns per workgroup; K split into the most
+  // pieces that keep the grid within one workgroup per CU and >= 512 of K per piece
+  p.stream = true;
+  p.bm = M <= 32 ? 32 : M <= 64 ? 64 : 128;
+  const int tiles = (N + ST_COLS - 1) / ST_COLS;
+  int s = 1;
+  while (s + 1 <= max_splits && tiles * (s + 1) <= 256 && K / (s + 1) >= 512) ++s;
+  p.k_chunk = (((K + s - 1) / s) + ST_KS - 1) / ST_KS * ST_KS;
+  p.splits = (K + p.k_chunk - 1) / p.k_chunk;
   return p;
 }
 
@@ -863,8 +514,8 @@ hipError_t gemm_launch(const GemmArgs& a, int epi, const GemmPlan& p, hipStream_
                        hipEvent_t e1) {
   // packed activations in, or a packed SwiGLU output: the streaming and the big-tile kernels
   // (and the split-K reduction) with K % 32 == 0 and F % 32 == 0
-  if ((a.a_packed && (a.K % 32 || !(p.stream || p.big) || (epi == EPI_SWIGLU && a.N % 64 != 0))) ||
-      (a.c_kt && (!(p.stream || p.big) || epi != EPI_SWIGLU || a.N % 64 != 0 || a.c_kt * 64 != a.N)))
+  if ((a.a_packed && (a.K % 32 || !(p.stream || p.wide) || (epi == EPI_SWIGLU && a.N % 64 != 0))) ||
+      (a.c_kt && (!(p.stream || p.wide) || epi != EPI_SWIGLU || a.N % 64 != 0 || a.c_kt * 64 != a.N)))
     return hipErrorInvalidValue;
   switch (epi) {
     case EPI_BF16: return launch_epi<EPI_BF16>(a, p, st, reduce, e0, e1);

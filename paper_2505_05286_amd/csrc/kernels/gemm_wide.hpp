@@ -1,0 +1,273 @@
+// bf16 "NT" GEMM of more than 64-128 rows: C[M,N] = A[M,K] * B[N,K]^T with the weights read
+// straight into registers.  Instantiated by gemm_wide_*.hip, one epilogue each.
+#pragma once
+
+#include "gemm_util.hpp"
+
+namespace hxf {
+
+namespace {
+
+// More than 64-128 rows: macro tiles of 16 TM rows x 256 columns on the 16x16x32 MFMA, four
+// wavefronts, each owning all the tile's rows and 64 of its columns.  The weights go straight
+// from memory to registers (a wavefront's columns are its own, so nothing is read twice in a
+// workgroup; a packed tile is one contiguous kilobyte per load), R steps of 32 of K ahead;
+// only the activations pass through LDS, stages of 64 of K by buffer DMA, NS in flight.
+//
+// Why: with both operands in LDS and 8 wavefronts the CU's LDS port (128 B/cycle) was the
+// bound: 192 x 256 tiles read 0.83 KB and wrote 0.29 KB per 32x32x16 MFMA, of the 1 KB per
+// MFMA the port has; here an A fragment feeds four MFMAs and only A is written (0.6 KB).  One
+// wavefront per SIMD keeps the accumulators (4 TM registers x 4) in AGPRs and needs its own
+// overlap: the A fragments of step k + 1 are read into the registers that step k has just
+// used, one LDS read after every four MFMAs, and the barrier of a stage lies half a stage
+// before its first use.  Measured (2080 rows, back to back, against 8 wavefronts with both
+// operands in LDS): 57344 x 8192 SwiGLU from row-major activations 1970 -> 1512 us
+// (1.29 PFLOP/s), 6144 x 4096 112 -> 89, 4096 x 14336 290 -> 227; 32x32x16 MFMAs on this
+// scheme are 5% slower, 8 steps of weights ahead 5-7%, 2 steps 2-4%, two workgroups per CU of
+// half the rows 5-10%.  With 8 wavefronts (144 rows x 512 columns, two per SIMD) 8192 x 28672
+// takes 847 us against 927 in the best tile of 4: 240 tiles, one round of the chip.
+//
+// Row-major activations are staged as 8 rows x 128 bytes per DMA (whole cache lines), with
+// the eight 16-byte chunks of row r stored in the order chunk ^ (r / 2 % 8), so that the 16
+// lanes of a fragment read touch 16 different 16-byte columns of LDS; packed activations are
+// 1 KB tiles in operand order already.  SwiGLU groups logical columns by 64 (32 gate rows,
+// then the 32 matching up rows) so one lane holds both.  Weights are the first MFMA operand,
+// so a lane ends up with 4 consecutive columns of one row and stores them together.
+// SPLIT: grid.y cuts K into chunks of k_chunk (a multiple of 64); each writes its fp32
+// partial [M][N] to slot blockIdx.y of a.partial (not with SwiGLU).
+template <int TM, int R, int EPI, bool SPLIT, int WV, int OCC>
+__global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
+  constexpr int BM = 16 * TM, BN = 64 * WV, NS = 4;
+  constexpr int A_BLK = TM * 2, A_PW = (A_BLK + WV - 1) / WV, STAGE = A_BLK * 512;   // 1 KB blocks per stage, per wavefront
+  constexpr bool SW = (EPI == EPI_SWIGLU);
+  // outstanding loads allowed when stage s + 1 must have landed: the younger stages' DMAs and
+  // the weight loads issued since its own DMAs (the first four of the same pass may have been
+  // scheduled before those)
+  constexpr int WAIT = (NS - 3) * A_PW + 8 * (NS - 2) - 4;
+  static_assert((2 * NS) % R == 0 && WAIT < 64 && 4 * R + (NS - 2) * A_PW < 64, "pipeline");
+  static_assert(NS * STAGE * 2 <= 160 * 1024, "stage layout");
+  static_assert(!(SW && SPLIT), "split partials hold logical columns; SwiGLU needs both halves summed first");
+  __shared__ __attribute__((aligned(1024))) bf16_t L0[STAGE], L1[STAGE], L2[STAGE], L3[STAGE];
+  auto slot = [&](auto ic) -> bf16_t* {
+    constexpr int I = decltype(ic)::value % NS;
+    if constexpr (I == 0) return L0; else if constexpr (I == 1) return L1; else if constexpr (I == 2) return L2;
+    else return L3;
+  };
+  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
+  const int L = xcd_remap(blockIdx.x, tiles_m * tiles_n);
+  const int tn = L / tiles_m, tm = L % tiles_m;
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kb = SPLIT ? blockIdx.y * (a.k_chunk / 32) : 0;              // first step (32 of K)
+  const int kt = (SPLIT ? min(a.kt, kb + a.k_chunk / 32) : a.kt) - kb;   // steps
+  const int nst = (kt + 1) / 2;                                          // stages (64 of K)
+
+  // activation DMA: block (row tile rt, kk) of the stage; packed: the tile's half kk; row-major:
+  // rows 8 kk .. 8 kk + 7 of the tile (rows past M repeat the last one; never stored)
+  const int rows_left = a.M - m0;
+  const rsrc_t ra = a.a_packed
+      ? make_rsrc(a.A + (size_t)(m0 / 16) * a.kt * 512, (uint32_t)min(TM, (rows_left + 15) / 16) * a.kt * 1024)
+      : make_rsrc(a.A + (size_t)m0 * a.lda, (uint32_t)((min(BM, rows_left) - 1) * a.lda + a.K) * 2);
+  const int k_end = (a.a_packed ? a.kt * 32 : a.K) - kb * 32 - (nst - 1) * 64;   // of the last stage
+  int a_off[A_PW], a_dst[A_PW];
+  bool a_in[A_PW];   // the lane's chunk of the last stage lies inside K
+#pragma unroll
+  for (int u = 0; u < A_PW; ++u) {
+    const int b = min(w * A_PW + u, A_BLK - 1), rt = b >> 1, kk = b & 1;
+    const int r8 = kk * 8 + (lane >> 3), ch = (lane & 7) ^ (r8 >> 1);
+    a_dst[u] = b * 512;
+    a_in[u] = (a.a_packed ? kk * 32 : ch * 8) < k_end;
+    a_off[u] = 2 * (a.a_packed ? (min(rt, (rows_left - 1) / 16) * a.kt + kk) * 512 + lane * 8
+                               : min(rt * 16 + r8, rows_left - 1) * a.lda + ch * 8);
+  }
+  const int a_step = a.a_packed ? 2048 : 128, a_first = (kb / 2) * a_step;   // bytes per stage (kb is even)
+  auto issue_a = [&](int s, bf16_t* base) __attribute__((always_inline)) {
+    const int ss = min(s, nst - 1);   // past the last stage: reload it (never read)
+    const bool last = ss == nst - 1;
+#pragma unroll
+    for (int u = 0; u < A_PW; ++u)
+      buf_dma16(ra, (last && !a_in[u]) ? kOutOfRange : a_off[u], a_first + ss * a_step, base + a_dst[u]);
+  };
+  // weights: the wavefront's four column tiles (tiles past N: zeros, or the last one again)
+  const int b_tiles = ((SW ? a.N / 2 : a.N) + 15) / 16;
+  const int c0 = min(n0 + w * 64, a.N - 1) & ~15;
+  const int bt = SW ? (c0 >> 6) * 2 + ((c0 >> 4) & 1) : c0 >> 4;   // first tile of the matrix (SwiGLU: of both)
+  const uint32_t b_bytes = (uint32_t)min(4, b_tiles - bt) * a.kt * 1024;
+  const rsrc_t rb0 = make_rsrc(a.B + (size_t)bt * a.kt * 512, b_bytes);
+  const rsrc_t rb1 = SW ? make_rsrc(a.B2 + (size_t)bt * a.kt * 512, b_bytes) : rb0;
+  int b_off[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) b_off[j] = lane * 16 + (SW ? (j & 1) : j) * a.kt * 1024;
+  uint4 fb[R][4];
+  auto load_b = [&](auto rc, int k) __attribute__((always_inline)) {
+    constexpr int r = decltype(rc)::value % R;
+    const int kk = kb + min(k, kt - 1);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) fb[r][j] = buf_load16(j < 2 ? rb0 : rb1, b_off[j], kk * 1024);
+  };
+  f32x4 acc[TM][4];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 fa[TM];
+  // LDS offset of the lane's fragment in a row tile, by step of the stage
+  int f_off[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    f_off[h] = a.a_packed ? h * 512 + lane * 8
+                          : (lane & 15) * 64 + (((h * 4 + (lane >> 4)) ^ ((lane & 15) >> 1)) * 8);
+  auto read_a = [&](const bf16_t* base, int i, int h) __attribute__((always_inline)) {
+    return as_bf16x8(*reinterpret_cast<const uint4*>(base + i * 1024 + f_off[h]));
+  };
+  // one step with the weights of ring slot r; reads the next step's fragments as it goes
+  auto step = [&](auto rc, const bf16_t* next, int h) __attribute__((always_inline)) {
+    constexpr int r = decltype(rc)::value % R;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = mfma16x16x32(as_bf16x8(fb[r][j]), fa[i], acc[i][j]);
+      fa[i] = read_a(next, i, h);
+    }
+    static_for<TM>([&](auto) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);   // four MFMAs
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+    });
+  };
+  static_for<NS - 1>([&](auto ic) {
+    issue_a(decltype(ic)::value, slot(ic));
+    __builtin_amdgcn_sched_barrier(0);   // the waits below count in this order
+  });
+  static_for<R>([&](auto ic) { load_b(ic, decltype(ic)::value); });
+  __builtin_amdgcn_sched_barrier(0);
+  wait_vmcnt<4 * R + (NS - 2) * A_PW>();
+  __builtin_amdgcn_s_barrier();
+#pragma unroll
+  for (int i = 0; i < TM; ++i) fa[i] = read_a(L0, i, 0);
+  step(std::integral_constant<int, 0>{}, L0, 1);
+  load_b(std::integral_constant<int, 0>{}, R);
+  __builtin_amdgcn_sched_barrier(0);
+  // pass s: the second step of stage s (it reads stage s + 1's first fragments) and the first
+  // of stage s + 1.  Every LDS read follows, without a branch, the wait for its stage's DMA,
+  // and the loop has one exit: otherwise the compiler adds waits for everything in flight.
+  int s0 = 0;
+  for (; s0 + NS <= (kt - 1) / 2; s0 += NS) {
+    static_for<NS>([&](auto ic) {
+      constexpr int J = decltype(ic)::value;
+      wait_vmcnt<WAIT>();
+      __builtin_amdgcn_s_barrier();
+      issue_a(s0 + J + NS - 1, slot(std::integral_constant<int, J + NS - 1>{}));
+      const bf16_t* next = slot(std::integral_constant<int, J + 1>{});
+      step(std::integral_constant<int, 2 * J + 1>{}, next, 0);
+      load_b(std::integral_constant<int, 2 * J + 1>{}, (s0 + J) * 2 + 1 + R);
+      __builtin_amdgcn_sched_barrier(0);
+      step(std::integral_constant<int, 2 * J + 2>{}, next, 1);
+      load_b(std::integral_constant<int, 2 * J + 2>{}, (s0 + J) * 2 + 2 + R);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  }
+  // the remaining steps one by one (at most 2 NS), the ring shifted by copies
+  auto dyn_slot = [&](int i) -> bf16_t* {
+    i %= NS;
+    return i == 0 ? L0 : i == 1 ? L1 : i == 2 ? L2 : L3;
+  };
+  for (int k = 2 * s0 + 1; k < kt; ++k) {
+    if (k & 1) {
+      wait_vmcnt<0>();
+      __builtin_amdgcn_s_barrier();
+      issue_a((k >> 1) + NS - 1, dyn_slot((k >> 1) + NS - 1));
+    }
+    step(std::integral_constant<int, 1>{}, dyn_slot((k >> 1) + (k & 1)), (k & 1) ^ 1);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+#pragma unroll
+      for (int r = 1; r < R; ++r) fb[r][j] = fb[(r + 1) % R][j];
+    }
+    load_b(std::integral_constant<int, 0>{}, k + R);
+  }
+  wait_vmcnt<0>();
+
+  // lane holds row l % 16 and columns 4 (l / 16) .. + 3 of each 16 x 16 tile
+  const int col4 = (lane >> 4) * 4;
+  float* P = SPLIT ? a.partial + (size_t)blockIdx.y * a.M * a.N : nullptr;
+  const int ld = SPLIT ? a.N : a.ldc;
+  // four columns at once where every group of four is whole and aligned
+  const bool vec = SW && a.c_kt ? ((uintptr_t)a.C & 7) == 0
+                                : ((ld | a.N) & 3) == 0 && ((SPLIT ? (uintptr_t)P : (uintptr_t)a.C) & 15) == 0;
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int row = m0 + i * 16 + (lane & 15);
+    if (row >= a.M) continue;
+    if constexpr (SW) {
+      if (n0 + w * 64 >= a.N) continue;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int oc = ((n0 + w * 64) >> 6) * 32 + j * 16 + col4;
+        float o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float g = acc[i][j][e];
+          o[e] = g / (1.f + __expf(-g)) * acc[i][j + 2][e];
+        }
+        bf16_t* c = reinterpret_cast<bf16_t*>(a.C) + (a.c_kt ? packed_elem(row, oc, a.c_kt) : (size_t)row * a.ldc + oc);
+        if (vec) {
+          *reinterpret_cast<uint2*>(c) = make_uint2(pack_bf2(o[0], o[1]), pack_bf2(o[2], o[3]));
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) c[e] = f2bf(o[e]);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int col = n0 + w * 64 + j * 16 + col4;
+        if (col >= a.N) continue;
+        const size_t o = (size_t)row * ld + col;
+        const f32x4 v = acc[i][j];
+        if constexpr (EPI == EPI_BF16 && !SPLIT) {
+          bf16_t* c = reinterpret_cast<bf16_t*>(a.C) + o;
+          if (vec) {
+            *reinterpret_cast<uint2*>(c) = make_uint2(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]));
+          } else {
+            for (int e = 0; e < 4 && col + e < a.N; ++e) c[e] = f2bf(v[e]);
+          }
+        } else {
+          float* c = (SPLIT ? P : reinterpret_cast<float*>(a.C)) + o;
+          constexpr bool ADD = EPI == EPI_RESID && !SPLIT;
+          if (vec) {
+            float4 x = ADD ? *reinterpret_cast<const float4*>(c) : make_float4(0.f, 0.f, 0.f, 0.f);
+            *reinterpret_cast<float4*>(c) = ADD ? make_float4(x.x + v[0], x.y + v[1], x.z + v[2], x.w + v[3])
+                                                : make_float4(v[0], v[1], v[2], v[3]);
+          } else {
+            for (int e = 0; e < 4 && col + e < a.N; ++e) c[e] = ADD ? c[e] + v[e] : v[e];
+          }
+        }
+      }
+    }
+  }
+}
+
+// Shapes: 16 tm rows (tm 4 .. 16) x 64 wv columns; wv = 8 with tm = 9 only.
+template <int TM, int WV, int EPI, bool SPLIT>
+hipError_t launch_wide(const GemmArgs& a, int S, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  constexpr int BM = 16 * TM, BN = 64 * WV, R = WV == 8 ? 2 : 4, OCC = WV / 4;
+  const int nb = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
+  return launch_ev(gemm_wide_kernel<TM, R, EPI, SPLIT, WV, OCC>, dim3(nb, S), dim3(64 * WV), st, e0, e1, a);
+}
+
+template <int EPI, bool SPLIT>
+hipError_t launch_wide_cfg(const GemmArgs& a, const GemmPlan& p, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  if (p.wv == 8) return p.tm == 9 ? launch_wide<9, 8, EPI, SPLIT>(a, p.splits, st, e0, e1) : hipErrorInvalidValue;
+  switch (p.tm) {
+#define HXF_WIDE(T) \
+  case T: return launch_wide<T, 4, EPI, SPLIT>(a, p.splits, st, e0, e1);
+    HXF_WIDE(4) HXF_WIDE(5) HXF_WIDE(6) HXF_WIDE(7) HXF_WIDE(8) HXF_WIDE(9) HXF_WIDE(10) HXF_WIDE(11) HXF_WIDE(12)
+    HXF_WIDE(13) HXF_WIDE(14) HXF_WIDE(15) HXF_WIDE(16)
+#undef HXF_WIDE
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace
+
+}  // namespace hxf

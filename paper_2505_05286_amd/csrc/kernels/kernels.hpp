@@ -48,10 +48,13 @@ struct GemmArgs {
   int c_kt;            // SwiGLU: > 0 writes C in the packed tile layout with c_kt tiles per row tile
 };
 
+// Bytes of the split-K partials array behind hxf_op_gemm_noalloc
+constexpr int64_t kNoallocPartials = int64_t(16) << 20;
+
 struct GemmPlan {
   bool stream = false;  // decode-sized M: LDS-DMA weight-streaming kernel
-  bool big = false;     // prefill-sized M: LDS-DMA 32x32x16 MFMA kernel
-  int cfg = 0;          // big kernel: macro-tile configuration
+  bool wide = false;    // more rows: macro tiles of 16 tm x 64 wv, weights straight to registers
+  int tm = 0, wv = 4;   // wide kernel: row tiles and wavefronts of a workgroup
   int bm = 128;
   int bn = 128;
   int splits = 1;
@@ -65,6 +68,12 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu = false);
 // events recorded at the first kernel's start and the last kernel's end.
 hipError_t gemm_launch(const GemmArgs& a, int epi, const GemmPlan& p, hipStream_t st, bool reduce = true,
                        hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+// The wide kernel with one epilogue each (gemm_wide_*.hip); a.k_chunk set, no reduction.
+hipError_t gemm_wide_bf16(const GemmArgs& a, const GemmPlan& p, hipStream_t st, hipEvent_t e0, hipEvent_t e1);
+hipError_t gemm_wide_resid(const GemmArgs& a, const GemmPlan& p, hipStream_t st, hipEvent_t e0, hipEvent_t e1);
+hipError_t gemm_wide_swiglu(const GemmArgs& a, const GemmPlan& p, hipStream_t st, hipEvent_t e0, hipEvent_t e1);
+hipError_t gemm_wide_f32(const GemmArgs& a, const GemmPlan& p, hipStream_t st, hipEvent_t e0, hipEvent_t e1);
+hipError_t gemm_wide_split(const GemmArgs& a, const GemmPlan& p, hipStream_t st, hipEvent_t e0, hipEvent_t e1);
 // Weight packing: W bf16 [N, K] row-major -> tiles of 16 rows x 32 columns in MFMA
 // operand order, zero padded to ceil(N/16)*16 rows and ceil(K/32)*32 columns.
 size_t packed_weight_elems(int N, int K);

@@ -14,6 +14,7 @@ using namespace hxf;
 namespace {
 
 constexpr int64_t kScratchBytes = HXF_GEMM_NOALLOC_MAX_BYTES;
+static_assert(kScratchBytes == kNoallocPartials, "the size gemm_plan keeps small plans within");
 
 // One copy per GPU, held until the process ends.  In host code `scratch` names a
 // host-side stand-in: kernels get the device address from hipGetSymbolAddress.

@@ -84,6 +84,37 @@ def test_gemm_swiglu(M_, N, K):
     _gemm_case(M_, N, K, hxf.EPI_SWIGLU, seed=M_ + N + K)
 
 
+@pytest.mark.parametrize("M_,N,K", [(65, 16384, 96), (81, 16390, 200), (112, 16401, 64), (129, 16400, 72),
+                                    (144, 16384, 352), (161, 16500, 320), (177, 16384, 264), (193, 16640, 32),
+                                    (209, 16384, 40), (225, 16448, 680), (241, 16384, 1000), (257, 16384, 8),
+                                    (130, 261, 1544), (300, 1002, 4096), (2080, 8192, 192), (577, 8190, 328)])
+@pytest.mark.parametrize("epi", [hxf.EPI_BF16, hxf.EPI_RESID])
+def test_gemm_wide_tile_edges(M_, N, K, epi):
+    """Every tile height of the register-weight kernel (a row count just inside it), outputs whose
+    rows are no multiple of four columns (element stores), K that ends inside a stage, a step or the
+    first step, split and unsplit, and the eight-wavefront shape.  The activation rows are longer
+    than K and hold NaN past it: nothing beyond K may reach a product."""
+    t = torch()
+    rng = np.random.default_rng(M_ + N + K + epi)
+    ab, af = rand_bf16(rng, (M_, K))
+    bb, bf = rand_bf16(rng, (N, K), 0.05)
+    lda = K + 24
+    padded = np.full((M_, lda), 0x7FC0, np.uint16)
+    padded[:, :K] = ab
+    A, B = dev_bits(padded), dev_packed(bb)
+    wsn = hxf.op_gemm_workspace_bytes(M_, N, K)
+    ws = t.empty(max(wsn, 256), dtype=t.uint8, device="cuda:0")
+    base = rng.standard_normal((M_, N)).astype(np.float32)
+    C = empty_i16(M_ * N) if epi == hxf.EPI_BF16 else t.from_numpy(base.copy()).to("cuda:0")
+    log(f"gemm wide edges M={M_} N={N} K={K} epi={epi} ws={wsn}")
+    hxf.op_gemm(A.data_ptr(), lda, B.data_ptr(), 0, C.data_ptr(), N, M_, N, K, epi, ws.data_ptr(), wsn)
+    t.cuda.synchronize()
+    rows = np.unique(np.concatenate([np.arange(0, M_, 37), np.arange(max(0, M_ - 20), M_)]))
+    ref = af[rows] @ bf.T + (base[rows].astype(np.float64) if epi == hxf.EPI_RESID else 0.0)
+    got = (host_f64(C) if epi == hxf.EPI_BF16 else C.cpu().numpy().astype(np.float64)).reshape(M_, N)[rows]
+    np.testing.assert_allclose(got, ref, rtol=2 ** -7 if epi == hxf.EPI_BF16 else 1e-5, atol=2e-4 * np.max(np.abs(ref)))
+
+
 @pytest.mark.parametrize("name,M_,N,K,epi", [
     ("8B qkv", 2080, 6144, 4096, hxf.EPI_BF16), ("8B o", 2080, 4096, 4096, hxf.EPI_RESID),
     ("8B gate/up", 2080, 2 * 14336, 4096, hxf.EPI_SWIGLU), ("8B down", 2080, 4096, 14336, hxf.EPI_RESID),
