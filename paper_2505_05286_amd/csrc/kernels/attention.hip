@@ -313,19 +313,27 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeAttnArgs a) {
   else out[0] = f2bf(acc[0] * inv);
 }
 
-// Chunked-prefill causal attention, one workgroup per (chunk, kv-head, block of
-// 128·PT/G queries): the 128·PT (query, head) pairs of the block are the columns of
+// Chunked-prefill causal attention, one workgroup per (chunk, kv-head, block of 128/G
+// queries): the 128 (query, head) pairs of the block are the columns of
 //   S^T[32 keys x 32 pairs] = K[32 x dh] . Q^T[dh x 32]       (v_mfma_f32_32x32x16_bf16)
 //   O^T[32 dims x 32 pairs] += V^T[32 x 32 keys] . P^T[32 x 32]
-// (PT tiles of 32 pairs per wavefront; the library launches PT = 1, 128 pairs per
-// workgroup).  Tiles of 32 keys (two pages) of K and V are moved into LDS by the DMA
-// path, five tiles in flight, and shared by the four wavefronts.  A lane of the S^T
+// with 32 pairs per wavefront.  Tiles of 32 keys (two pages) of K and V are moved into LDS
+// by the DMA path, five in flight, and shared by the four wavefronts.  A lane of the S^T
 // accumulator holds keys 8m + 4h + i (h = lane / 32) of its pair; taken in the order
 // m = 2s, 2s + 1 these are the 8 keys of the P^T operand for the 16-key step s (page s
 // of the tile); the V pool stores each page row with its tokens in that order (see
 // v_pos), so the V^T operand of a lane is one contiguous 16-byte LDS read.  Softmax is
 // online in log2 units, one exchange of the wavefront halves per tile for the max.
-template <int DH, int PT>
+//
+// A step multiplies K of tile t + 1 and V of tile t, so that the scores of the next tile and
+// the exponentials of this one run side by side in a wavefront; the tiles come by buffer DMA,
+// whose count leaves the LDS reads their own (with global_load_lds every LDS wait was a full
+// one).  What bounds it: LDS reads (each wavefront reads every K and V byte for its 32 pairs,
+// 1 KB per MFMA), exponentials and MFMAs each take 40-50% of a step, and the two wavefronts
+// of a SIMD overlap them only in part.  2048 queries at position 0 / 2048 / 6144: 54.9 / 112.4
+// / 252 us -> 54.2 / 108.7 / 233 (1.03 PFLOP/s).  The order of interleave() against the
+// compiler's own: 54.6 / 109.0 / 237.
+template <int DH>
 __global__ __launch_bounds__(256) void prefill_flash_kernel(PrefillAttnArgs a) {
   constexpr int KS = DH / 16;                  // 16-dim steps of QK^T
   constexpr int DT = DH / 32;                  // 32-dim tiles of O^T
@@ -334,7 +342,7 @@ __global__ __launch_bounds__(256) void prefill_flash_kernel(PrefillAttnArgs a) {
   constexpr int K_W = KT / 512 / 4;            // 16-byte DMA instructions per wavefront for K
   constexpr int V_W = KT / 512 / 4;            // and for V
   constexpr int PER_W = K_W + V_W;
-  constexpr int NS = 5;                        // key tiles in flight: NS - 1 ahead of the one computed
+  constexpr int NS = 5;                        // key tiles in LDS: the one multiplied, the next, three on their way
   __shared__ __attribute__((aligned(1024))) bf16_t L0[STAGE], L1[STAGE], L2[STAGE], L3[STAGE], L4[STAGE];
   auto slot = [&](auto ic) -> bf16_t* {
     constexpr int I = decltype(ic)::value % NS;
@@ -357,20 +365,18 @@ __global__ __launch_bounds__(256) void prefill_flash_kernel(PrefillAttnArgs a) {
       (const __attribute__((address_space(4))) int32_t*)(a.bt + (size_t)it.entry * a.bt_stride);
   const int h = lane >> 5;
 
-  // this lane's pairs (column lane % 32 of each of the wavefront's PT pair tiles)
-  int qpos[PT];
-  bf16x8 qf[PT][KS];
-#pragma unroll
-  for (int pt = 0; pt < PT; ++pt) {
-    const int p = (w * PT + pt) * 32 + (lane & 31);
-    const bool ok = p < npairs;
-    const int qi = ok ? p / G : 0, hj = ok ? p % G : 0;
-    qpos[pt] = ok ? pos0 + it.q0 + qi : -1;     // -1: every key masked
+  // this lane's pair (column lane % 32 of the wavefront's 32)
+  const int pair = w * 32 + (lane & 31);
+  const bool pair_ok = pair < npairs;
+  const int qi = pair_ok ? pair / G : 0, hj = pair_ok ? pair % G : 0;
+  const int qpos = pair_ok ? pos0 + it.q0 + qi : -1;   // -1: every key masked
+  bf16x8 qf[KS];
+  {
     const uint16_t* qrow = a.q + (size_t)(a.row0[it.entry] + it.q0 + qi) * a.q_stride + (it.kvh * G + hj) * DH;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      const uint4 v = ok ? *reinterpret_cast<const uint4*>(qrow + ks * 16 + h * 8) : make_uint4(0, 0, 0, 0);
-      qf[pt][ks] = as_bf16x8(v);
+      const uint4 v = pair_ok ? *reinterpret_cast<const uint4*>(qrow + ks * 16 + h * 8) : make_uint4(0, 0, 0, 0);
+      qf[ks] = as_bf16x8(v);
     }
   }
 
@@ -384,206 +390,237 @@ __global__ __launch_bounds__(256) void prefill_flash_kernel(PrefillAttnArgs a) {
     return bt[min(tt * 2 + pg, last_page)];
   };
   auto issue = [&](int entry, bf16_t* base) __attribute__((always_inline)) {
+    // one descriptor per page tile (scalar work only): the pools may exceed 4 GB
     const size_t tile = kv_tile(it.kvh, a.n_blocks, entry, DH);
+    const rsrc_t rk = make_rsrc(a.k_pool + tile, KT), rv = make_rsrc(a.v_pool + tile, KT);   // KT / 2 elements
 #pragma unroll
     for (int u = 0; u < K_W; ++u) {
       const int blk = w * K_W + u;               // 1 KB block of the K tile
-      dma16(a.k_pool + tile + (blk % (KT / 1024)) * 512 + lane * 8, base + blk * 512);
+      buf_dma16(rk, lane * 16, (blk % (KT / 1024)) * 1024, base + blk * 512);
     }
 #pragma unroll
     for (int u = 0; u < V_W; ++u) {
       const int blk = w * V_W + u;               // 1 KB block of the V tile
       // the two 16-byte halves of dims 8..15 (mod 16) of a block swap places in LDS, so that
       // the 16 lanes of one V^T read pass hit distinct banks
-      dma16(a.v_pool + tile + (blk % (KT / 1024)) * 512 + (lane ^ ((lane >> 4) & 1)) * 8, base + KT + blk * 512);
+      buf_dma16(rv, (lane ^ ((lane >> 4) & 1)) * 16, (blk % (KT / 1024)) * 1024, base + KT + blk * 512);
     }
   };
 
-  f32x16 o[PT][DT];
+  f32x16 o[DT];
 #pragma unroll
-  for (int pt = 0; pt < PT; ++pt)
+  for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) o[pt][dt][e] = 0.f;
-  // running maxima start finite, so that fully masked pairs keep zero weights, never NaN
-  float m[PT], l[PT];
-#pragma unroll
-  for (int pt = 0; pt < PT; ++pt) {
-    m[pt] = -1e30f;
-    l[pt] = 0.f;
-  }
+    for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
+  // the running maximum starts finite, so that a fully masked pair keeps zero weights, never NaN
+  float m = -1e30f, l = 0.f;
   // operand offsets inside a stage: K for key lane%32 (page (lane%32)/16), dims chunk ks*2 + h;
   // V^T for dim dt*32 + lane%32, page s, positions 8h..8h+7
   const int k_off = ((lane & 31) >> 4) * (KT / 2) + (lane & 15) * 8 + h * 128;
   const int v_off = KT + (lane & 31) * 16 + (h ^ ((lane >> 3) & 1)) * 8;
 
-  // One key tile.  Every LDS operand of the tile is requested first: the K fragments feed
-  // the QK^T chain as they arrive, and the V^T fragments are in registers by the time the
-  // softmax is done, so a wavefront alone on its SIMD does not wait on LDS between MFMAs.
-  auto compute = [&](const bf16_t* base, int t) __attribute__((always_inline)) {
-    bf16x8 kf[KS];
+  // raw scores of one key tile (K fragments from its stage)
+  bf16x8 kf[KS];
+  auto read_k = [&](const bf16_t* base) __attribute__((always_inline)) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) kf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(base + k_off + ks * 256));
-    uint4 vv[2][DT];
+  };
+  auto scores = [&]() __attribute__((always_inline)) {
+    f32x16 x;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) x[e] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) x = mfma32x32x16(kf[ks], qf[ks], x);
+    return x;
+  };
+  // raw-score maximum of the pair, scaled (the scale is positive)
+  auto score_max = [&](const f32x16& x) __attribute__((always_inline)) {
+    float v = x[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) v = fmaxf(v, x[r]);
+    return half_swap_max(v) * a.scale_log2;
+  };
+  // Before tile t's probabilities: the causal and context-end mask where the tile needs one
+  // (wavefront-uniform), then one wavefront-wide decision to move the reference maximum: it
+  // moves only when a score exceeds it by more than 2^8 (the exponentials then stay below
+  // 256, harmless in fp32 and bf16).
+  auto settle = [&](f32x16& x, float& mx, int t) __attribute__((always_inline)) {
+    const int k0 = (tbase + t) * 32;
+    if ((k0 + 32 > kend) || (k0 + 31 > pos0 + it.q0)) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int key = k0 + (r >> 2) * 8 + h * 4 + (r & 3);
+        if (key > qpos || key >= kend) x[r] = kNegInf;
+      }
+      mx = score_max(x);
+    }
+    if (__any(mx > m + 8.f)) {
+      const float m_new = fmaxf(m, mx);
+      const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+      m = m_new;
+      l *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[dt][e] *= alpha;
+    }
+  };
+  // V^T fragments of a tile; past the end of the context (LAST: the item's last tile) the
+  // entries are zeroed (garbage may be NaN)
+  uint4 vv[2][DT];
+  auto read_v = [&](const bf16_t* base) __attribute__((always_inline)) {
 #pragma unroll
     for (int st = 0; st < 2; ++st)
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) vv[st][dt] = *reinterpret_cast<const uint4*>(base + v_off + (st * DH + dt * 32) * 16);
-    f32x16 s[PT];
-#pragma unroll
-    for (int pt = 0; pt < PT; ++pt)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) s[pt][e] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-      for (int pt = 0; pt < PT; ++pt) s[pt] = mfma32x32x16(kf[ks], qf[pt][ks], s[pt]);
+  };
+  auto cut_v = [&](int t) __attribute__((always_inline)) {
     const int k0 = (tbase + t) * 32;
-    const bool edge = (k0 + 32 > kend) || (k0 + 31 > pos0 + it.q0);   // wavefront-uniform: a mask is needed
-    if (edge) {
+    if (k0 + 32 <= kend) return;
 #pragma unroll
-      for (int pt = 0; pt < PT; ++pt)
+    for (int st = 0; st < 2; ++st) {
+      const int tok0 = k0 + st * 16 + h * 4;    // keys of this lane's k slots: tok0 + 0..3, tok0 + 8..11
+      const uint2 lo = keep_mask(kend - tok0), hi = keep_mask(kend - tok0 - 8);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = k0 + (r >> 2) * 8 + h * 4 + (r & 3);
-          if (key > qpos[pt] || key >= kend) s[pt][r] = kNegInf;
-        }
-    }
-    // raw-score maxima (the scale is positive), then one wavefront-wide decision for
-    // all pair tiles: the reference max only moves when a score exceeds it by more
-    // than 2^8 (the exponentials then stay below 256, harmless in fp32 and bf16)
-    float mx[PT];
-#pragma unroll
-    for (int pt = 0; pt < PT; ++pt) {
-      float v = s[pt][0];
-#pragma unroll
-      for (int r = 1; r < 16; ++r) v = fmaxf(v, s[pt][r]);
-      mx[pt] = half_swap_max(v) * a.scale_log2;
-    }
-    bool grow = false;
-#pragma unroll
-    for (int pt = 0; pt < PT; ++pt) grow = grow || mx[pt] > m[pt] + 8.f;
-    if (__any(grow)) {
-#pragma unroll
-      for (int pt = 0; pt < PT; ++pt) {
-        const float m_new = fmaxf(m[pt], mx[pt]);
-        const float alpha = __builtin_amdgcn_exp2f(m[pt] - m_new);
-        m[pt] = m_new;
-        l[pt] *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) o[pt][dt][e] *= alpha;
+      for (int dt = 0; dt < DT; ++dt) {
+        vv[st][dt].x &= lo.x;
+        vv[st][dt].y &= lo.y;
+        vv[st][dt].z &= hi.x;
+        vv[st][dt].w &= hi.y;
       }
     }
-    bf16x8 pf[PT][2];
+  };
+  // probabilities of a tile (bf16 P^T operands), added to the denominator
+  bf16x8 pf[2];
+  auto probs = [&](const f32x16& x) __attribute__((always_inline)) {
+    float ps = 0.f;
+    float pv[16];
 #pragma unroll
-    for (int pt = 0; pt < PT; ++pt) {
-      float ps = 0.f;
-      float pv[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        pv[r] = __builtin_amdgcn_exp2f(fmaf(s[pt][r], a.scale_log2, -m[pt]));   // masked: exp2(-inf) = 0
-        ps += pv[r];
-      }
-      l[pt] += ps;
-#pragma unroll
-      for (int st = 0; st < 2; ++st) {
-        bf16x8 v;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = (__bf16)pv[st * 8 + j];
-        pf[pt][st] = v;
-      }
+    for (int r = 0; r < 16; ++r) {
+      pv[r] = __builtin_amdgcn_exp2f(fmaf(x[r], a.scale_log2, -m));   // masked: exp2(-inf) = 0
+      ps += pv[r];
     }
-    // V^T . P^T; past the end of the context the V entries are zeroed (garbage may be NaN)
-    if (k0 + 32 > kend) {
+    l += ps;
 #pragma unroll
-      for (int st = 0; st < 2; ++st) {
-        const int tok0 = k0 + st * 16 + h * 4;    // keys of this lane's k slots: tok0 + 0..3, tok0 + 8..11
-        const uint2 lo = keep_mask(kend - tok0), hi = keep_mask(kend - tok0 - 8);
+    for (int st = 0; st < 2; ++st) {
+      bf16x8 v;
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          vv[st][dt].x &= lo.x;
-          vv[st][dt].y &= lo.y;
-          vv[st][dt].z &= hi.x;
-          vv[st][dt].w &= hi.y;
-        }
-      }
+      for (int j = 0; j < 8; ++j) v[j] = (__bf16)pv[st * 8 + j];
+      pf[st] = v;
     }
+  };
+  auto accumulate = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int st = 0; st < 2; ++st)
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int pt = 0; pt < PT; ++pt) o[pt][dt] = mfma32x32x16(as_bf16x8(vv[st][dt]), pf[pt][st], o[pt][dt]);
+      for (int dt = 0; dt < DT; ++dt) o[dt] = mfma32x32x16(as_bf16x8(vv[st][dt]), pf[st], o[dt]);
+  };
+
+  // order of a step: the K reads, the first exponentials, then one MFMA at a time (QK^T of the
+  // next tile, then V^T . P^T) with a V read and softmax work between
+  auto interleave = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_group_barrier(0x100, KS, 0);   // LDS reads
+    __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);    // VALU
+    __builtin_amdgcn_sched_group_barrier(0x400, 4, 0);    // exponentials
+    static_for<KS>([&](auto) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+      __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);
+    });
+    static_for<2 * DT>([&](auto) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+      __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);
+    });
   };
 
   // The block-table entry of the DMA issued at a step is loaded at the end of the step
   // before (a scalar load that the wait at the loop head drains together with the DMA
   // wait), so that no LDS read waits on it.
-  static_for<NS - 1>([&](auto ic) { issue(entry_of(decltype(ic)::value), slot(ic)); });
+  static_for<NS - 1>([&](auto ic) {
+    issue(entry_of(decltype(ic)::value), slot(ic));
+    __builtin_amdgcn_sched_barrier(0);
+  });
   int next_entry = entry_of(NS - 1);
+  wait_vmcnt<(NS - 2) * PER_W>();
+  __builtin_amdgcn_s_barrier();
+  read_k(L0);
+  f32x16 s = scores();
+  float mx = score_max(s);
   int t0 = 0;
-  for (; t0 + NS <= ntiles; t0 += NS) {
+  for (; t0 + NS < ntiles; t0 += NS) {
     static_for<NS>([&](auto ic) {
       constexpr int J = decltype(ic)::value;
-      wait_vmcnt_lgkm0<(NS - 2) * PER_W>();
+      wait_vmcnt_lgkm0<(NS - 3) * PER_W>();   // tile t0 + J + 1 has landed
       __builtin_amdgcn_s_barrier();
       issue(next_entry, slot(std::integral_constant<int, J + NS - 1>{}));
-      __builtin_amdgcn_sched_barrier(0);   // the DMAs go out before this tile's LDS reads
-      compute(slot(ic), t0 + J);
+      settle(s, mx, t0 + J);
+      __builtin_amdgcn_sched_barrier(0);
+      read_k(slot(std::integral_constant<int, J + 1>{}));
+      read_v(slot(ic));
+      probs(s);
+      const f32x16 next = scores();
+      accumulate();
+      mx = score_max(next);
+      s = next;
+      interleave();
       __builtin_amdgcn_sched_barrier(0);
       next_entry = entry_of(t0 + J + NS);
     });
   }
+  // the last 1 .. NS tiles: all but the fifth are in LDS or on their way
+  wait_vmcnt_lgkm0<63>();
+  __builtin_amdgcn_s_barrier();
+  if (t0 + NS - 1 < ntiles) issue(next_entry, slot(std::integral_constant<int, NS - 1>{}));
   wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
-  static_for<NS - 1>([&](auto ic) {
+  static_for<NS>([&](auto ic) {
     constexpr int J = decltype(ic)::value;
-    if (t0 + J < ntiles) compute(slot(ic), t0 + J);
+    if (t0 + J < ntiles) {
+      settle(s, mx, t0 + J);
+      read_v(slot(ic));
+      if (t0 + J + 1 < ntiles) {
+        read_k(slot(std::integral_constant<int, J + 1>{}));
+        probs(s);
+        const f32x16 next = scores();
+        accumulate();
+        mx = score_max(next);
+        s = next;
+      } else {
+        probs(s);
+        cut_v(t0 + J);
+        accumulate();
+      }
+    }
   });
 
   // O^T lane holds pair lane % 32 and dims dt*32 + 8*(r/4) + 4h + r%4
-  float lt[PT];
-#pragma unroll
-  for (int pt = 0; pt < PT; ++pt) lt[pt] = l[pt] + __shfl_xor(l[pt], 32, kWave);
+  const float lt = l + __shfl_xor(l, 32, kWave);
+  if (!pair_ok) return;
   if (it.part >= 0) {
     // a part of a split item: unnormalized output, max and sum for the merge
-#pragma unroll
-    for (int pt = 0; pt < PT; ++pt) {
-      const int p = (w * PT + pt) * 32 + (lane & 31);
-      if (p >= npairs) continue;
-      float* po = a.part_o + ((size_t)it.part * kPrefillPairs + p) * DH;
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4)
-          *reinterpret_cast<float4*>(po + dt * 32 + g4 * 8 + h * 4) =
-              make_float4(o[pt][dt][g4 * 4], o[pt][dt][g4 * 4 + 1], o[pt][dt][g4 * 4 + 2], o[pt][dt][g4 * 4 + 3]);
-      if (h == 0)
-        *reinterpret_cast<float2*>(a.part_ml + ((size_t)it.part * kPrefillPairs + p) * 2) = make_float2(m[pt], lt[pt]);
-    }
-    return;
-  }
-#pragma unroll
-  for (int pt = 0; pt < PT; ++pt) {
-    const int p = (w * PT + pt) * 32 + (lane & 31);
-    if (p >= npairs) continue;
-    const float inv = 1.f / lt[pt];
-    const int qi = p / G, hj = p % G;
-    const int orow = a.row0[it.entry] + it.q0 + qi, col0 = (it.kvh * G + hj) * DH;
+    float* po = a.part_o + ((size_t)it.part * kPrefillPairs + pair) * DH;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const int d = dt * 32 + g4 * 8 + h * 4;   // 4 columns inside one 8-column group
-        const size_t at = a.out_kt ? packed_elem(orow, col0 + d, a.out_kt) : (size_t)orow * a.out_stride + col0 + d;
-        *reinterpret_cast<uint2*>(a.out + at) =
-            make_uint2(pack_bf2(o[pt][dt][g4 * 4] * inv, o[pt][dt][g4 * 4 + 1] * inv),
-                       pack_bf2(o[pt][dt][g4 * 4 + 2] * inv, o[pt][dt][g4 * 4 + 3] * inv));
-      }
+      for (int g4 = 0; g4 < 4; ++g4)
+        *reinterpret_cast<float4*>(po + dt * 32 + g4 * 8 + h * 4) =
+            make_float4(o[dt][g4 * 4], o[dt][g4 * 4 + 1], o[dt][g4 * 4 + 2], o[dt][g4 * 4 + 3]);
+    if (h == 0) *reinterpret_cast<float2*>(a.part_ml + ((size_t)it.part * kPrefillPairs + pair) * 2) = make_float2(m, lt);
+    return;
   }
+  const float inv = 1.f / lt;
+  const int orow = a.row0[it.entry] + it.q0 + qi, col0 = (it.kvh * G + hj) * DH;
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4) {
+      const int d = dt * 32 + g4 * 8 + h * 4;   // 4 columns inside one 8-column group
+      const size_t at = a.out_kt ? packed_elem(orow, col0 + d, a.out_kt) : (size_t)orow * a.out_stride + col0 + d;
+      *reinterpret_cast<uint2*>(a.out + at) = make_uint2(pack_bf2(o[dt][g4 * 4] * inv, o[dt][g4 * 4 + 1] * inv),
+                                                         pack_bf2(o[dt][g4 * 4 + 2] * inv, o[dt][g4 * 4 + 3] * inv));
+    }
 }
 
 // Log-sum-exp merge of the key-range parts of split prefill items: DH/8 lanes per
@@ -650,10 +687,6 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(PrefillAttnArgs a) {
 
 }  // namespace
 
-// pair tiles of 32 (query, head) pairs per wavefront in the prefill kernel
-constexpr int kPrefillPT = 1;
-
-static_assert(4 * 32 * kPrefillPT == kPrefillPairs, "pairs of a prefill item");
 int prefill_queries_per_item(int group) { return kPrefillPairs / group; }
 
 // With events, they take the kernel's own start and end timestamps; without, a plain
@@ -702,8 +735,8 @@ hipError_t prefill_attn_launch(const PrefillAttnArgs& a, hipStream_t st, hipEven
     else hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, a);
     return hipGetLastError();
   };
-  hipError_t e = a.dh == 128 ? go(prefill_flash_kernel<128, kPrefillPT>, dim3(a.n_items), ev_start, e1)
-                             : go(prefill_flash_kernel<64, kPrefillPT>, dim3(a.n_items), ev_start, e1);
+  hipError_t e = a.dh == 128 ? go(prefill_flash_kernel<128>, dim3(a.n_items), ev_start, e1)
+                             : go(prefill_flash_kernel<64>, dim3(a.n_items), ev_start, e1);
   if (e != hipSuccess || a.n_merges <= 0) return e;
   // workgroups per merge job: 128 pairs x dh / 8 threads over 256-thread workgroups
   const unsigned grid = (unsigned)a.n_merges * (kPrefillPairs * (a.dh / 8) / 256);
