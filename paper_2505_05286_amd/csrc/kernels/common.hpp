@@ -69,25 +69,13 @@ __device__ __forceinline__ T wave_max(T v) {
   return v;
 }
 
-// ---- LDS DMA (global_load_lds_dwordx4): each lane moves 16 bytes from its own
-// global address to lds_block + 16 * lane, without passing through registers;
-// completion is counted by vmcnt.
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-typedef __attribute__((address_space(1))) void* global_ptr_t;
-
-__device__ __forceinline__ void dma16(const void* g, void* lds_block) {
-  __builtin_amdgcn_global_load_lds((global_ptr_t)g, (lds_ptr_t)lds_block, 16, 0, 0);
-}
-// The same with the non-temporal hint (data read once: the decode GEMMs' weight stream)
-__device__ __forceinline__ void dma16_nt(const void* g, void* lds_block) {
-  __builtin_amdgcn_global_load_lds((global_ptr_t)g, (lds_ptr_t)lds_block, 16, 0, 2);
-}
-
-// ---- The same DMA and 16-byte loads through a buffer descriptor (MUBUF).  A global_load_lds
-// is a FLAT instruction to the compiler: while one is in flight it can only wait for every
-// LDS read and every load at once.  Buffer accesses are counted exactly, so LDS reads and
+// ---- LDS DMA: each lane moves 16 bytes from its own address to lds_block + 16 * lane,
+// without passing through registers; completion is counted by vmcnt.  It goes through a
+// buffer descriptor (MUBUF), because a global_load_lds is a FLAT instruction to the compiler:
+// while one is in flight it can only wait for every LDS read and every load at once.  Buffer accesses are counted exactly, so LDS reads and
 // loads stay in flight across the uses of older ones; their address is a 32-bit lane offset
 // plus a scalar offset (no 64-bit VALU adds), and a lane offset at or past `bytes` reads zeros.
+typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 constexpr int kOutOfRange = (int)0x80000000u;   // a lane offset past every buffer
 

@@ -1,5 +1,4 @@
-// bf16 "NT" GEMM of more than 64-128 rows: C[M,N] = A[M,K] * B[N,K]^T with the weights read
-// straight into registers.  Instantiated by gemm_wide_*.hip, one epilogue each.
+// bf16 "NT" GEMM C[M,N] = A[M,K] * B[N,K]^T with the weights read straight into registers.  Instantiated by gemm_wide_*.hip, one epilogue each.
 #pragma once
 
 #include "gemm_util.hpp"
@@ -8,8 +7,9 @@ namespace hxf {
 
 namespace {
 
-// More than 64-128 rows: macro tiles of 16 TM rows x 256 columns on the 16x16x32 MFMA, four
-// wavefronts, each owning all the tile's rows and 64 of its columns.  The weights go straight
+// Macro tiles of 16 TM rows x 16 NW WV columns on the 16x16x32 MFMA: WV wavefronts, each
+// owning all the tile's rows and 16 NW of its columns (NW = 4, or 2 for the few rows of a
+// decode step, where narrow tiles fill the chip).  The weights go straight
 // from memory to registers (a wavefront's columns are its own, so nothing is read twice in a
 // workgroup; a packed tile is one contiguous kilobyte per load), R steps of 32 of K ahead;
 // only the activations pass through LDS, stages of 64 of K by buffer DMA, NS in flight.
@@ -19,7 +19,7 @@ namespace {
 // MFMA the port has; here an A fragment feeds four MFMAs and only A is written (0.6 KB).  One
 // wavefront per SIMD keeps the accumulators (4 TM registers x 4) in AGPRs and needs its own
 // overlap: the A fragments of step k + 1 are read into the registers that step k has just
-// used, one LDS read after every four MFMAs, and the barrier of a stage lies half a stage
+// used, one LDS read after every NW MFMAs, and the barrier of a stage lies half a stage
 // before its first use.  Measured (2080 rows, back to back, against 8 wavefronts with both
 // operands in LDS): 57344 x 8192 SwiGLU from row-major activations 1970 -> 1512 us
 // (1.29 PFLOP/s), 6144 x 4096 112 -> 89, 4096 x 14336 290 -> 227; 32x32x16 MFMAs on this
@@ -27,26 +27,33 @@ namespace {
 // half the rows 5-10%.  With 8 wavefronts (144 rows x 512 columns, two per SIMD) 8192 x 28672
 // takes 847 us against 927 in the best tile of 4: 240 tiles, one round of the chip.
 //
+// Up to 128 rows the bytes of the weights are the bound: non-temporal loads where one row of
+// tiles reads them (55296 x 5120 at 64 rows 101.4 -> 93.0 us, 128256 x 4096 201 -> 182), and
+// against a kernel with the weights in LDS: one row 37.5 -> 36.0 us (28672 x 4096) and 19.4 ->
+// 17.3 (4096 x 14336), 64 rows 44.5 -> 41.2 and 24.4 -> 24.0, 64 x 128256 x 4096 203 -> 182.
+//
 // Row-major activations are staged as 8 rows x 128 bytes per DMA (whole cache lines), with
 // the eight 16-byte chunks of row r stored in the order chunk ^ (r / 2 % 8), so that the 16
 // lanes of a fragment read touch 16 different 16-byte columns of LDS; packed activations are
 // 1 KB tiles in operand order already.  SwiGLU groups logical columns by 64 (32 gate rows,
-// then the 32 matching up rows) so one lane holds both.  Weights are the first MFMA operand,
+// then the 32 matching up rows; by 32 with NW = 2) so one lane holds both.  Weights are the first MFMA operand,
 // so a lane ends up with 4 consecutive columns of one row and stores them together.
 // SPLIT: grid.y cuts K into chunks of k_chunk (a multiple of 64); each writes its fp32
-// partial [M][N] to slot blockIdx.y of a.partial (not with SwiGLU).
-template <int TM, int R, int EPI, bool SPLIT, int WV, int OCC>
+// partial [M][N] to slot blockIdx.y of a.partial (SwiGLU: with NW = 2, logical columns in
+// groups of 16 gate and 16 up).
+template <int TM, int NW, int R, int EPI, bool SPLIT, int WV, int OCC, int CACHE>
 __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
-  constexpr int BM = 16 * TM, BN = 64 * WV, NS = 4;
+  constexpr int BM = 16 * TM, BN = 16 * NW * WV, NS = 4;
   constexpr int A_BLK = TM * 2, A_PW = (A_BLK + WV - 1) / WV, STAGE = A_BLK * 512;   // 1 KB blocks per stage, per wavefront
   constexpr bool SW = (EPI == EPI_SWIGLU);
   // outstanding loads allowed when stage s + 1 must have landed: the younger stages' DMAs and
-  // the weight loads issued since its own DMAs (the first four of the same pass may have been
+  // the weight loads issued since its own DMAs (the first step's of the same pass may have been
   // scheduled before those)
-  constexpr int WAIT = (NS - 3) * A_PW + 8 * (NS - 2) - 4;
-  static_assert((2 * NS) % R == 0 && WAIT < 64 && 4 * R + (NS - 2) * A_PW < 64, "pipeline");
+  constexpr int WAIT = (NS - 3) * A_PW + 2 * NW * (NS - 2) - NW;
+  static_assert((2 * NS) % R == 0 && WAIT < 64 && NW * R + (NS - 2) * A_PW < 64, "pipeline");
+  static_assert(!SW || NW % 2 == 0, "a wavefront holds as many up columns as gate columns");
   static_assert(NS * STAGE * 2 <= 160 * 1024, "stage layout");
-  static_assert(!(SW && SPLIT), "split partials hold logical columns; SwiGLU needs both halves summed first");
+  static_assert(!(SW && SPLIT) || NW == 2, "partials hold logical columns in groups of 16 gate and 16 up");
   __shared__ __attribute__((aligned(1024))) bf16_t L0[STAGE], L1[STAGE], L2[STAGE], L3[STAGE];
   auto slot = [&](auto ic) -> bf16_t* {
     constexpr int I = decltype(ic)::value % NS;
@@ -82,34 +89,36 @@ __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
   }
   const int a_step = a.a_packed ? 2048 : 128, a_first = (kb / 2) * a_step;   // bytes per stage (kb is even)
   auto issue_a = [&](int s, bf16_t* base) __attribute__((always_inline)) {
-    const int ss = min(s, nst - 1);   // past the last stage: reload it (never read)
-    const bool last = ss == nst - 1;
+    const int ss = min(s, nst - 1);
+    const bool last = s == nst - 1, past = s >= nst;   // past the last stage: zeros
 #pragma unroll
     for (int u = 0; u < A_PW; ++u)
-      buf_dma16(ra, (last && !a_in[u]) ? kOutOfRange : a_off[u], a_first + ss * a_step, base + a_dst[u]);
+      buf_dma16(ra, past || (last && !a_in[u]) ? kOutOfRange : a_off[u], a_first + ss * a_step, base + a_dst[u]);
   };
-  // weights: the wavefront's four column tiles (tiles past N: zeros, or the last one again)
-  const int b_tiles = ((SW ? a.N / 2 : a.N) + 15) / 16;
-  const int c0 = min(n0 + w * 64, a.N - 1) & ~15;
-  const int bt = SW ? (c0 >> 6) * 2 + ((c0 >> 4) & 1) : c0 >> 4;   // first tile of the matrix (SwiGLU: of both)
-  const uint32_t b_bytes = (uint32_t)min(4, b_tiles - bt) * a.kt * 1024;
+  // weights: the wavefront's NW column tiles, for SwiGLU NW / 2 of the gate and the same NW / 2 of
+  // the up matrix (tiles past N: zeros, or the last one again)
+  constexpr int HALF = SW ? NW / 2 : NW;
+  const int n_out = SW ? a.N / 2 : a.N, c0 = (n0 + w * NW * 16) / (SW ? 2 : 1);   // output columns, the wavefront's first
+  const int b_tiles = (n_out + 15) / 16, bt = min(c0 / 16, b_tiles - 1);
+  const uint32_t b_bytes = (uint32_t)min(HALF, b_tiles - bt) * a.kt * 1024;
   const rsrc_t rb0 = make_rsrc(a.B + (size_t)bt * a.kt * 512, b_bytes);
   const rsrc_t rb1 = SW ? make_rsrc(a.B2 + (size_t)bt * a.kt * 512, b_bytes) : rb0;
-  int b_off[4];
+  int b_off[HALF];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) b_off[j] = lane * 16 + (SW ? (j & 1) : j) * a.kt * 1024;
-  uint4 fb[R][4];
+  for (int j = 0; j < HALF; ++j) b_off[j] = lane * 16 + j * a.kt * 1024;
+  uint4 fb[R][NW];
   auto load_b = [&](auto rc, int k) __attribute__((always_inline)) {
     constexpr int r = decltype(rc)::value % R;
     const int kk = kb + min(k, kt - 1);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) fb[r][j] = buf_load16(j < 2 ? rb0 : rb1, b_off[j], kk * 1024);
+    for (int j = 0; j < NW; ++j)   // past the last step: zeros
+      fb[r][j] = buf_load16<CACHE>(j < HALF ? rb0 : rb1, k < kt ? b_off[j % HALF] : kOutOfRange, kk * 1024);
   };
-  f32x4 acc[TM][4];
+  f32x4 acc[TM][NW];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   bf16x8 fa[TM];
   // LDS offset of the lane's fragment in a row tile, by step of the stage
   int f_off[2];
@@ -126,12 +135,12 @@ __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = mfma16x16x32(as_bf16x8(fb[r][j]), fa[i], acc[i][j]);
+      for (int j = 0; j < NW; ++j) acc[i][j] = mfma16x16x32(as_bf16x8(fb[r][j]), fa[i], acc[i][j]);
       fa[i] = read_a(next, i, h);
     }
     static_for<TM>([&](auto) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);   // four MFMAs
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+      __builtin_amdgcn_sched_group_barrier(0x008, NW, 0);   // MFMAs
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);    // one LDS read
     });
   };
   static_for<NS - 1>([&](auto ic) {
@@ -140,7 +149,7 @@ __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
   });
   static_for<R>([&](auto ic) { load_b(ic, decltype(ic)::value); });
   __builtin_amdgcn_sched_barrier(0);
-  wait_vmcnt<4 * R + (NS - 2) * A_PW>();
+  wait_vmcnt<NW * R + (NS - 2) * A_PW>();
   __builtin_amdgcn_s_barrier();
 #pragma unroll
   for (int i = 0; i < TM; ++i) fa[i] = read_a(L0, i, 0);
@@ -150,8 +159,11 @@ __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
   // pass s: the second step of stage s (it reads stage s + 1's first fragments) and the first
   // of stage s + 1.  Every LDS read follows, without a branch, the wait for its stage's DMA,
   // and the loop has one exit: otherwise the compiler adds waits for everything in flight.
+  // Whole trips of 2 NS steps; a last trip that has at least three steps of its own runs on
+  // over zeros (0 x 0 in both operands), which costs less than so many single steps.
+  const int s_end = (kt - 1 + 2 * NS - 3) / (2 * NS) * NS;
   int s0 = 0;
-  for (; s0 + NS <= (kt - 1) / 2; s0 += NS) {
+  for (; s0 < s_end; s0 += NS) {
     static_for<NS>([&](auto ic) {
       constexpr int J = decltype(ic)::value;
       wait_vmcnt<WAIT>();
@@ -166,7 +178,7 @@ __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
       __builtin_amdgcn_sched_barrier(0);
     });
   }
-  // the remaining steps one by one (at most 2 NS), the ring shifted by copies
+  // one or two remaining steps singly, the ring shifted by copies
   auto dyn_slot = [&](int i) -> bf16_t* {
     i %= NS;
     return i == 0 ? L0 : i == 1 ? L1 : i == 2 ? L2 : L3;
@@ -179,7 +191,7 @@ __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
     }
     step(std::integral_constant<int, 1>{}, dyn_slot((k >> 1) + (k & 1)), (k & 1) ^ 1);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < NW; ++j) {
 #pragma unroll
       for (int r = 1; r < R; ++r) fb[r][j] = fb[(r + 1) % R][j];
     }
@@ -192,22 +204,22 @@ __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
   float* P = SPLIT ? a.partial + (size_t)blockIdx.y * a.M * a.N : nullptr;
   const int ld = SPLIT ? a.N : a.ldc;
   // four columns at once where every group of four is whole and aligned
-  const bool vec = SW && a.c_kt ? ((uintptr_t)a.C & 7) == 0
+  const bool vec = SW && !SPLIT && a.c_kt ? ((uintptr_t)a.C & 7) == 0
                                 : ((ld | a.N) & 3) == 0 && ((SPLIT ? (uintptr_t)P : (uintptr_t)a.C) & 15) == 0;
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int row = m0 + i * 16 + (lane & 15);
     if (row >= a.M) continue;
-    if constexpr (SW) {
-      if (n0 + w * 64 >= a.N) continue;
+    if constexpr (SW && !SPLIT) {
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int oc = ((n0 + w * 64) >> 6) * 32 + j * 16 + col4;
+      for (int j = 0; j < HALF; ++j) {
+        const int oc = c0 + j * 16 + col4;
+        if (oc >= n_out) continue;
         float o[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float g = acc[i][j][e];
-          o[e] = g / (1.f + __expf(-g)) * acc[i][j + 2][e];
+          o[e] = g / (1.f + __expf(-g)) * acc[i][j + HALF][e];
         }
         bf16_t* c = reinterpret_cast<bf16_t*>(a.C) + (a.c_kt ? packed_elem(row, oc, a.c_kt) : (size_t)row * a.ldc + oc);
         if (vec) {
@@ -219,8 +231,8 @@ __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
       }
     } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int col = n0 + w * 64 + j * 16 + col4;
+      for (int j = 0; j < NW; ++j) {
+        const int col = n0 + (w * NW + j) * 16 + col4;
         if (col >= a.N) continue;
         const size_t o = (size_t)row * ld + col;
         const f32x4 v = acc[i][j];
@@ -247,25 +259,33 @@ __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
   }
 }
 
-// Shapes: 16 tm rows (tm 4 .. 16) x 64 wv columns; wv = 8 with tm = 9 only.
-template <int TM, int WV, int EPI, bool SPLIT>
-hipError_t launch_wide(const GemmArgs& a, int S, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
-  constexpr int BM = 16 * TM, BN = 64 * WV, R = WV == 8 ? 2 : 4, OCC = WV / 4;
+// Shapes: 16 tm rows x 16 nw wv columns.  Weights that one row of tiles reads (tiles_m == 1) are
+// fetched with the non-temporal hint (p.once).
+template <int TM, int NW, int WV, int CACHE, int EPI, bool SPLIT>
+hipError_t launch_wide(const GemmArgs& a, const GemmPlan& p, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  constexpr int BM = 16 * TM, BN = 16 * NW * WV, R = WV == 8 ? 2 : NW == 2 ? 8 : 4, OCC = WV / 4;
   const int nb = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  return launch_ev(gemm_wide_kernel<TM, R, EPI, SPLIT, WV, OCC>, dim3(nb, S), dim3(64 * WV), st, e0, e1, a);
+  return launch_ev(gemm_wide_kernel<TM, NW, R, EPI, SPLIT, WV, OCC, CACHE>, dim3(nb, p.splits), dim3(64 * WV), st, e0,
+                   e1, a);
 }
 
 template <int EPI, bool SPLIT>
 hipError_t launch_wide_cfg(const GemmArgs& a, const GemmPlan& p, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
-  if (p.wv == 8) return p.tm == 9 ? launch_wide<9, 8, EPI, SPLIT>(a, p.splits, st, e0, e1) : hipErrorInvalidValue;
-  switch (p.tm) {
-#define HXF_WIDE(T) \
-  case T: return launch_wide<T, 4, EPI, SPLIT>(a, p.splits, st, e0, e1);
-    HXF_WIDE(4) HXF_WIDE(5) HXF_WIDE(6) HXF_WIDE(7) HXF_WIDE(8) HXF_WIDE(9) HXF_WIDE(10) HXF_WIDE(11) HXF_WIDE(12)
-    HXF_WIDE(13) HXF_WIDE(14) HXF_WIDE(15) HXF_WIDE(16)
+#define HXF_WIDE(T, NW, WV, CACHE) \
+  case T: return launch_wide<T, NW, WV, CACHE, EPI, SPLIT>(a, p, st, e0, e1);
+  if (p.wv == 8) switch (p.tm) { HXF_WIDE(9, 4, 8, 0) }
+  else if (p.nw == 2) switch (p.tm) { HXF_WIDE(1, 2, 4, 2) HXF_WIDE(2, 2, 4, 2) HXF_WIDE(4, 2, 4, 2) HXF_WIDE(8, 2, 4, 2) }
+  else if (p.once) switch (p.tm) {
+      HXF_WIDE(1, 4, 4, 2) HXF_WIDE(2, 4, 4, 2) HXF_WIDE(4, 4, 4, 2) HXF_WIDE(6, 4, 4, 2) HXF_WIDE(8, 4, 4, 2)
+      HXF_WIDE(10, 4, 4, 2) HXF_WIDE(12, 4, 4, 2) HXF_WIDE(14, 4, 4, 2) HXF_WIDE(16, 4, 4, 2)
+    }
+  else switch (p.tm) {
+      HXF_WIDE(4, 4, 4, 0) HXF_WIDE(5, 4, 4, 0) HXF_WIDE(6, 4, 4, 0) HXF_WIDE(7, 4, 4, 0) HXF_WIDE(8, 4, 4, 0)
+      HXF_WIDE(9, 4, 4, 0) HXF_WIDE(10, 4, 4, 0) HXF_WIDE(11, 4, 4, 0) HXF_WIDE(12, 4, 4, 0) HXF_WIDE(13, 4, 4, 0)
+      HXF_WIDE(14, 4, 4, 0) HXF_WIDE(15, 4, 4, 0) HXF_WIDE(16, 4, 4, 0)
+    }
 #undef HXF_WIDE
-    default: return hipErrorInvalidValue;
-  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace

@@ -44,7 +44,7 @@ struct GemmArgs {
   int lda, ldc;
   int k_chunk;
   int kt;              // K tiles of the packed weights, ceil(K / 32)
-  int a_packed;        // A is in the packed tile layout (lda unused); streaming and big-tile kernels
+  int a_packed;        // A is in the packed tile layout (lda unused)
   int c_kt;            // SwiGLU: > 0 writes C in the packed tile layout with c_kt tiles per row tile
 };
 
@@ -52,11 +52,8 @@ struct GemmArgs {
 constexpr int64_t kNoallocPartials = int64_t(16) << 20;
 
 struct GemmPlan {
-  bool stream = false;  // decode-sized M: LDS-DMA weight-streaming kernel
-  bool wide = false;    // more rows: macro tiles of 16 tm x 64 wv, weights straight to registers
-  int tm = 0, wv = 4;   // wide kernel: row tiles and wavefronts of a workgroup
-  int bm = 128;
-  int bn = 128;
+  int tm = 4, nw = 4, wv = 4;   // a workgroup's row tiles, column tiles per wavefront, wavefronts
+  bool once = false;            // one row of tiles: the weights are read once (non-temporal loads)
   int splits = 1;
   int k_chunk = 0;
 };

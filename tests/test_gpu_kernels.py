@@ -87,17 +87,21 @@ def test_gemm_swiglu(M_, N, K):
 @pytest.mark.parametrize("M_,N,K", [(65, 16384, 96), (81, 16390, 200), (112, 16401, 64), (129, 16400, 72),
                                     (144, 16384, 352), (161, 16500, 320), (177, 16384, 264), (193, 16640, 32),
                                     (209, 16384, 40), (225, 16448, 680), (241, 16384, 1000), (257, 16384, 8),
-                                    (130, 261, 1544), (300, 1002, 4096), (2080, 8192, 192), (577, 8190, 328)])
+                                    (130, 261, 1544), (300, 1002, 4096), (2080, 8192, 192), (577, 8190, 328),
+                                    (1, 128, 40), (17, 130, 552), (33, 2050, 1096), (128, 33000, 136), (90, 40000, 64)])
 @pytest.mark.parametrize("epi", [hxf.EPI_BF16, hxf.EPI_RESID])
 def test_gemm_wide_tile_edges(M_, N, K, epi):
     """Every tile height of the register-weight kernel (a row count just inside it), outputs whose
     rows are no multiple of four columns (element stores), K that ends inside a stage, a step or the
     first step, split and unsplit, and the eight-wavefront shape.  The activation rows are longer
-    than K and hold NaN past it: nothing beyond K may reach a product."""
+    than K and hold NaN past it: nothing beyond K may reach a product.  One activation is infinite:
+    steps run over zeros past K must not turn its row's infinities into NaN."""
     t = torch()
     rng = np.random.default_rng(M_ + N + K + epi)
     ab, af = rand_bf16(rng, (M_, K))
     bb, bf = rand_bf16(rng, (N, K), 0.05)
+    ab[M_ - 1, K - 1], af[M_ - 1, K - 1] = 0x7F80, np.inf
+    bb[bf == 0], bf[bf == 0] = 0x3F80, 1.0            # (infinity times zero is NaN)
     lda = K + 24
     padded = np.full((M_, lda), 0x7FC0, np.uint16)
     padded[:, :K] = ab
@@ -112,7 +116,8 @@ def test_gemm_wide_tile_edges(M_, N, K, epi):
     rows = np.unique(np.concatenate([np.arange(0, M_, 37), np.arange(max(0, M_ - 20), M_)]))
     ref = af[rows] @ bf.T + (base[rows].astype(np.float64) if epi == hxf.EPI_RESID else 0.0)
     got = (host_f64(C) if epi == hxf.EPI_BF16 else C.cpu().numpy().astype(np.float64)).reshape(M_, N)[rows]
-    np.testing.assert_allclose(got, ref, rtol=2 ** -7 if epi == hxf.EPI_BF16 else 1e-5, atol=2e-4 * np.max(np.abs(ref)))
+    scale = np.max(np.abs(ref[np.isfinite(ref)]), initial=1.0)
+    np.testing.assert_allclose(got, ref, rtol=2 ** -7 if epi == hxf.EPI_BF16 else 1e-5, atol=2e-4 * scale)
 
 
 @pytest.mark.parametrize("name,M_,N,K,epi", [
