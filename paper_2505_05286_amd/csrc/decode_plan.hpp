@@ -20,10 +20,25 @@ struct DecodeSeq {
 
 struct DecodePlan {
   std::vector<DecodeItem> items;    // one-tile items, then the n_wide two-tile items (each longest first)
-  int64_t n_wide = 0;
+  int64_t n_items = 0, n_wide = 0;
   std::vector<MergeItem> merges;    // one per (sequence, kv-head), in sequence order
   int64_t n_parts = 0;              // partial slots used
   int64_t kv_tokens = 0;            // (token, kv-head) pairs read: the sum of the item lengths
+
+  // the planner's working memory, kept so that a plan used again allocates nothing
+  struct Stream {
+    int32_t first, len;       // tokens [first, first + len)
+    int32_t rows, n_rows;     // sequences served: members[rows .. rows + n_rows)
+    int32_t piece, n_pieces;  // tokens per piece (the last may be shorter)
+    int32_t slot_off;         // offset of this stream's pieces inside each row's slot block
+  };
+  struct Run {                // the pieces of a stream that have one length
+    int32_t len, stream, piece0, n;
+  };
+  std::vector<Stream> streams;
+  std::vector<Run> runs;
+  std::vector<uint64_t> order;
+  std::vector<int32_t> members, shared, slots, base;
 };
 
 // Sequences whose block tables start with the same physical pages (forks of one
@@ -36,6 +51,10 @@ struct DecodePlan {
 // (decode_target_tokens), and the partials of a (sequence, kv-head) occupy
 // consecutive slots, merged by log-sum-exp.
 void plan_decode(const std::vector<DecodeSeq>& seqs, int hkv, int G, DecodePlan& out);
+// The same in two steps, for a caller that has the items written where they are uploaded from:
+// everything but `items` (left as it is), then the n_items records.
+void plan_decode_streams(const std::vector<DecodeSeq>& seqs, int hkv, int G, DecodePlan& out);
+void write_decode_items(const DecodePlan& plan, const std::vector<DecodeSeq>& seqs, int hkv, DecodeItem* items);
 
 // Chunked-prefill work list.  Each (prefill entry, kv-head, block of qpi queries) is
 // one item over the key tiles its queries see.  With fewer items than CUs, an item

@@ -340,21 +340,21 @@ int HipExecutor::run(const std::vector<BatchEntry>& batch, std::vector<int32_t>&
   plan_prefill(pentries, hkv, qpi, pplan_);
   const std::vector<PrefillItem>& pitems = pplan_.items;
   const std::vector<PrefillMerge>& pmerges = pplan_.merges;
-  plan_decode(dseqs, hkv, G, dplan_);
-  const std::vector<DecodeItem>& ditems = dplan_.items;
+  plan_decode_streams(dseqs, hkv, G, dplan_);
+  const int64_t n_ditems = dplan_.n_items;
   const std::vector<MergeItem>& merges = dplan_.merges;
-  if (dplan_.n_wide < 0 || dplan_.n_wide > (int64_t)ditems.size()) {
+  if (dplan_.n_wide < 0 || dplan_.n_wide > n_ditems) {
     err = "run: decode work list counts are inconsistent";
     return HXF_EINVAL;
   }
-  if ((int64_t)ditems.size() > plan_.dec_items_max || dplan_.n_parts > plan_.dec_items_max ||
+  if (n_ditems > plan_.dec_items_max || dplan_.n_parts > plan_.dec_items_max ||
       (int64_t)pitems.size() > plan_.pf_items_max || (int64_t)pmerges.size() > plan_.pf_merges_max ||
-      pplan_.n_parts > plan_.pf_parts_max || (graph && (int64_t)ditems.size() > item_cap)) {
+      pplan_.n_parts > plan_.pf_parts_max || (graph && n_ditems > item_cap)) {
     err = "run: attention work list exceeds the workspace plan";
     return HXF_EINVAL;
   }
   constexpr int64_t kItemWords = sizeof(DecodeItem) / 4;
-  const int64_t o_ditems = sec((graph ? item_cap : (int64_t)ditems.size()) * kItemWords),
+  const int64_t o_ditems = sec((graph ? item_cap : n_ditems) * kItemWords),
                 o_merges = sec((int64_t)merges.size() * 4),
                 o_pitems = sec((int64_t)pitems.size() * (int64_t)(sizeof(PrefillItem) / 4)),
                 o_pmerges = sec((int64_t)pmerges.size() * (int64_t)(sizeof(PrefillMerge) / 4));
@@ -362,10 +362,11 @@ int HipExecutor::run(const std::vector<BatchEntry>& batch, std::vector<int32_t>&
     err = "run: metadata exceeds the workspace plan";
     return HXF_EINVAL;
   }
-  const int64_t n_wide = dplan_.n_wide, n_narrow = (int64_t)ditems.size() - n_wide;
+  const int64_t n_wide = dplan_.n_wide, n_narrow = n_ditems - n_wide;
   hm[o_nitems] = (int32_t)n_narrow;
   hm[o_nitems + 1] = (int32_t)n_wide;
-  copy_vec(hm + o_ditems, ditems);
+  DecodeItem* ditems = reinterpret_cast<DecodeItem*>(hm + o_ditems);
+  write_decode_items(dplan_, dseqs, hkv, ditems);
   copy_vec(hm + o_merges, merges);
   copy_vec(hm + o_pitems, pitems);
   copy_vec(hm + o_pmerges, pmerges);
@@ -393,15 +394,15 @@ int HipExecutor::run(const std::vector<BatchEntry>& batch, std::vector<int32_t>&
         if (b < 0 || b >= s_.n_blocks) return fail("block-table entry outside the pool", e);
       }
     }
-    for (size_t i = 0; i < ditems.size(); ++i) {
+    for (int64_t i = 0; i < n_ditems; ++i) {
       const DecodeItem& d = ditems[i];
-      const int rows_max = (int64_t)i < n_narrow ? decode_rows_narrow(G) : decode_rows_wide(G);
+      const int rows_max = i < n_narrow ? decode_rows_narrow(G) : decode_rows_wide(G);
       if (d.kvh < 0 || d.kvh >= hkv || d.t0 < 0 || d.t0 >= d.t1 || d.n_rows < 1 || d.n_rows > rows_max)
-        return fail("decode item", (int64_t)i);
+        return fail("decode item", i);
       for (int k = 0; k < d.n_rows; ++k)
         if (d.entry[k] < 0 || d.entry[k] >= E || !batch[d.entry[k]].decode || d.t1 > ctx[d.entry[k]] ||
             d.part[k] < 0 || d.part[k] >= dplan_.n_parts)
-          return fail("decode item row", (int64_t)i);
+          return fail("decode item row", i);
     }
     for (size_t i = 0; i < merges.size(); ++i) {
       const MergeItem& mi = merges[i];

@@ -122,12 +122,6 @@ struct DecodeItem {
 // Rows one 16-column tile holds, and the rows a wide (two-tile) item holds, for GQA group G.
 inline int decode_rows_narrow(int G) { return std::max(1, std::min(kDecodeRows, 16 / G)); }
 inline int decode_rows_wide(int G) { return std::max(1, std::min(kDecodeRows, 32 / G)); }
-// Launch order of the decode items: longest first (equal lengths keep their
-// order), so that the wavefronts that start last, when the chip drains, are the
-// short tail partitions.  Partial slots are unchanged, so the merge is unaffected.
-inline void order_decode_items(DecodeItem* it, size_t n) {
-  std::stable_sort(it, it + n, [](const DecodeItem& x, const DecodeItem& y) { return x.t1 - x.t0 > y.t1 - y.t0; });
-}
 // Decode work split.  Each (sequence, kv-head) context is cut into equal, page-aligned
 // partitions no longer than a per-launch target.  With fewer (stream, kv-head) pairs than
 // the wavefronts the chip holds at once (two per SIMD at the one-tile kernel's register

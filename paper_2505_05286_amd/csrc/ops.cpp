@@ -24,6 +24,48 @@ struct DecodeLayout {
           total = 0;
 };
 
+// Host state of the attention calls, one per thread and kept between calls: the plans (whose
+// working memory is reused) and a pinned staging buffer for the work lists.  Every call waits
+// for its stream before it returns, so nothing reads the buffer afterwards, whatever stream
+// and device the next call uses.  Lists beyond kStageMax go through pageable memory, so that
+// the pinned memory a thread holds (until it ends) is bounded.
+constexpr size_t kStageMax = size_t(4) << 20;
+struct AttnHost {
+  DecodePlan decode;
+  PrefillPlan prefill;
+  std::vector<DecodeSeq> seqs;
+  std::vector<PrefillEntry> entries;
+  std::vector<uint8_t> pageable;
+  uint8_t* stage = nullptr;
+  size_t stage_bytes = 0;
+  ~AttnHost() {
+    if (stage) (void)hipHostFree(stage);
+  }
+  uint8_t* staging(size_t bytes) {
+    if (bytes <= kStageMax) {
+      if (bytes <= stage_bytes) return stage;
+      if (stage) (void)hipHostFree(stage);
+      stage = nullptr;
+      stage_bytes = 0;
+      size_t want = 64 << 10;
+      while (want < bytes) want *= 2;
+      void* p = nullptr;
+      if (hipHostMalloc(&p, want, hipHostMallocPortable) == hipSuccess) {
+        stage = static_cast<uint8_t*>(p);
+        stage_bytes = want;
+        return stage;
+      }
+      (void)hipGetLastError();
+    }
+    pageable.resize(bytes);
+    return pageable.data();
+  }
+};
+AttnHost& attn_host() {
+  static thread_local AttnHost h;
+  return h;
+}
+
 void decode_seqs(int B, const int32_t* ctx, const int32_t* bt_host, int bt_stride, std::vector<DecodeSeq>& seqs) {
   seqs.clear();
   for (int b = 0; b < B; ++b)
@@ -32,7 +74,7 @@ void decode_seqs(int B, const int32_t* ctx, const int32_t* bt_host, int bt_strid
 
 DecodeLayout decode_layout(const DecodePlan& P, int B, int Hq, int Hkv, int dh) {
   DecodeLayout L;
-  L.items = (int64_t)P.items.size();
+  L.items = P.n_items;
   L.merges = (int64_t)B * Hkv;
   L.parts = P.n_parts;
   const int G = Hq / Hkv;
@@ -152,10 +194,10 @@ int hxf_op_kv_scatter(const void* k, const void* v, const int32_t* slot, void* k
 int64_t hxf_op_decode_attention_workspace_bytes(int32_t B, int32_t Hq, int32_t Hkv, int32_t dh, const int32_t* ctx,
                                                 const int32_t* bt_host, int32_t bt_stride) {
   if (B < 0 || !ctx || !shapes_ok(Hq, Hkv, dh) || (bt_host && bt_stride <= 0)) return -1;
-  std::vector<DecodeSeq> seqs;
-  decode_seqs(B, ctx, bt_host, bt_stride, seqs);
-  DecodePlan P;
-  plan_decode(seqs, Hkv, Hq / Hkv, P);
+  AttnHost& H = attn_host();
+  decode_seqs(B, ctx, bt_host, bt_stride, H.seqs);
+  DecodePlan& P = H.decode;
+  plan_decode_streams(H.seqs, Hkv, Hq / Hkv, P);
   return decode_layout(P, B, Hq, Hkv, dh).total;
 }
 
@@ -165,15 +207,14 @@ int hxf_op_decode_plan(int32_t B, int32_t Hq, int32_t Hkv, const int32_t* ctx, c
   if (B < 0 || !ctx || Hq <= 0 || Hkv <= 0 || Hq % Hkv || Hq / Hkv > 16 || (bt_host && bt_stride <= 0) || !n_items ||
       !n_merges || (items_cap > 0 && !items) || (merges_cap > 0 && !merges))
     return HXF_EINVAL;
-  std::vector<DecodeSeq> seqs;
-  decode_seqs(B, ctx, bt_host, bt_stride, seqs);
-  DecodePlan P;
-  plan_decode(seqs, Hkv, Hq / Hkv, P);
-  *n_items = (int32_t)P.items.size();
+  AttnHost& H = attn_host();
+  decode_seqs(B, ctx, bt_host, bt_stride, H.seqs);
+  DecodePlan& P = H.decode;
+  plan_decode_streams(H.seqs, Hkv, Hq / Hkv, P);
+  *n_items = (int32_t)P.n_items;
   *n_merges = (int32_t)P.merges.size();
-  if ((int64_t)items_cap < (int64_t)P.items.size() || (int64_t)merges_cap < (int64_t)P.merges.size())
-    return HXF_ENOMEM;
-  copy_vec(items, P.items);
+  if ((int64_t)items_cap < P.n_items || (int64_t)merges_cap < (int64_t)P.merges.size()) return HXF_ENOMEM;
+  write_decode_items(P, H.seqs, Hkv, reinterpret_cast<DecodeItem*>(items));
   copy_vec(merges, P.merges);
   return HXF_OK;
 }
@@ -186,20 +227,20 @@ int hxf_op_decode_attention(const void* q, const void* k_pool, const void* v_poo
   if (B == 0) return HXF_OK;
   for (int b = 0; b < B; ++b)
     if (ctx[b] <= 0 || (ctx[b] + kPage - 1) / kPage > bt_stride) return HXF_EINVAL;
-  std::vector<DecodeSeq> seqs;
-  decode_seqs(B, ctx, bt_host, bt_stride, seqs);
-  DecodePlan P;
-  plan_decode(seqs, Hkv, Hq / Hkv, P);
+  AttnHost& H = attn_host();
+  decode_seqs(B, ctx, bt_host, bt_stride, H.seqs);
+  DecodePlan& P = H.decode;
+  plan_decode_streams(H.seqs, Hkv, Hq / Hkv, P);
   const DecodeLayout L = decode_layout(P, B, Hq, Hkv, dh);
   if (!workspace || ws_bytes < L.total) return HXF_ENOMEM;
-  std::vector<uint8_t> host(L.off_o);
-  copy_vec(host.data() + L.off_items, P.items);
-  copy_vec(host.data() + L.off_merges, P.merges);
-  auto* qrow = reinterpret_cast<int32_t*>(host.data() + L.off_qrow);
+  uint8_t* host = H.staging(L.off_o);
+  write_decode_items(P, H.seqs, Hkv, reinterpret_cast<DecodeItem*>(host + L.off_items));
+  copy_vec(host + L.off_merges, P.merges);
+  auto* qrow = reinterpret_cast<int32_t*>(host + L.off_qrow);
   for (int b = 0; b < B; ++b) qrow[b] = b;
   hipStream_t st = (hipStream_t)stream;
   uint8_t* ws = (uint8_t*)workspace;
-  if (hipMemcpyAsync(ws, host.data(), host.size(), hipMemcpyHostToDevice, st) != hipSuccess) return HXF_EDEVICE;
+  if (hipMemcpyAsync(ws, host, L.off_o, hipMemcpyHostToDevice, st) != hipSuccess) return HXF_EDEVICE;
   DecodeAttnArgs a{};
   a.q = (const uint16_t*)q;
   a.q_row = reinterpret_cast<const int32_t*>(ws + L.off_qrow);
@@ -210,7 +251,7 @@ int hxf_op_decode_attention(const void* q, const void* k_pool, const void* v_poo
   a.bt = bt;
   a.bt_stride = bt_stride;
   a.items = reinterpret_cast<const DecodeItem*>(ws + L.off_items);
-  a.n_items = (int)(P.items.size() - P.n_wide);
+  a.n_items = (int)(P.n_items - P.n_wide);
   a.n_wide = (int)P.n_wide;
   a.merges = reinterpret_cast<const MergeItem*>(ws + L.off_merges);
   a.n_merges = (int)L.merges;
@@ -222,8 +263,10 @@ int hxf_op_decode_attention(const void* q, const void* k_pool, const void* v_poo
   a.Hkv = Hkv;
   a.dh = dh;
   a.scale_log2 = 1.4426950408889634f / std::sqrt((float)dh);
-  if (decode_attn_launch(a, st) != hipSuccess || decode_merge_launch(a, st) != hipSuccess) return HXF_EDEVICE;
-  return dev_rc(hipStreamSynchronize(st));
+  // (the staging buffer is free again only after the wait, also when a launch failed)
+  const bool ok = decode_attn_launch(a, st) == hipSuccess && decode_merge_launch(a, st) == hipSuccess;
+  const hipError_t done = hipStreamSynchronize(st);
+  return ok ? dev_rc(done) : HXF_EDEVICE;
 }
 
 namespace {
@@ -270,12 +313,13 @@ int hxf_op_prefill_plan(int32_t S, int32_t Hq, int32_t Hkv, const int32_t* pos0,
   if (S < 0 || Hq <= 0 || Hkv <= 0 || Hq % Hkv || Hq / Hkv > 16 || (S > 0 && (!pos0 || !n_host)) || !n_items ||
       !n_merges || (items_cap > 0 && !items) || (merges_cap > 0 && !merges))
     return HXF_EINVAL;
-  std::vector<PrefillEntry> entries;
+  std::vector<PrefillEntry>& entries = attn_host().entries;
+  entries.clear();
   for (int s = 0; s < S; ++s) {
     if (n_host[s] < 0 || pos0[s] < 0) return HXF_EINVAL;
     if (n_host[s] > 0) entries.push_back(PrefillEntry{s, pos0[s], n_host[s]});
   }
-  PrefillPlan P;
+  PrefillPlan& P = attn_host().prefill;
   plan_prefill(entries, Hkv, prefill_queries_per_item(Hq / Hkv), P);
   *n_items = (int32_t)P.items.size();
   *n_merges = (int32_t)P.merges.size();
@@ -300,20 +344,22 @@ int hxf_op_prefill_attention(const void* q, const void* k_pool, const void* v_po
   const int64_t need = hxf_op_prefill_attention_workspace_bytes(S, Hq, Hkv, n_host);
   if (!workspace || ws_bytes < need) return HXF_ENOMEM;
   const int qpi = prefill_queries_per_item(Hq / Hkv);
-  std::vector<PrefillEntry> entries;
+  AttnHost& H = attn_host();
+  H.entries.clear();
   for (int s = 0; s < S; ++s)
-    if (n_host[s] > 0) entries.push_back(PrefillEntry{s, pos0[s], n_host[s]});
-  PrefillPlan P;
-  plan_prefill(entries, Hkv, qpi, P);
+    if (n_host[s] > 0) H.entries.push_back(PrefillEntry{s, pos0[s], n_host[s]});
+  PrefillPlan& P = H.prefill;
+  plan_prefill(H.entries, Hkv, qpi, P);
   const PrefillLayout L = prefill_layout(prefill_whole_items(S, Hkv, qpi, n_host), S, 128);
-  std::vector<uint8_t> host(L.off_rp + (int64_t)S * 8);
-  copy_vec(host.data(), P.items);
-  copy_vec(host.data() + L.off_merges, P.merges);
-  std::memcpy(host.data() + L.off_rp, row0, (size_t)S * 4);
-  std::memcpy(host.data() + L.off_rp + S * 4, pos0, (size_t)S * 4);
+  const size_t n_up = L.off_rp + (size_t)S * 8;
+  uint8_t* host = H.staging(n_up);
+  copy_vec(host, P.items);
+  copy_vec(host + L.off_merges, P.merges);
+  std::memcpy(host + L.off_rp, row0, (size_t)S * 4);
+  std::memcpy(host + L.off_rp + S * 4, pos0, (size_t)S * 4);
   hipStream_t st = (hipStream_t)stream;
   uint8_t* ws = (uint8_t*)workspace;
-  if (hipMemcpyAsync(ws, host.data(), host.size(), hipMemcpyHostToDevice, st) != hipSuccess) return HXF_EDEVICE;
+  if (hipMemcpyAsync(ws, host, n_up, hipMemcpyHostToDevice, st) != hipSuccess) return HXF_EDEVICE;
   PrefillAttnArgs a{};
   a.q = (const uint16_t*)q;
   a.q_stride = Hq * dh;
@@ -336,8 +382,9 @@ int hxf_op_prefill_attention(const void* q, const void* k_pool, const void* v_po
   a.Hkv = Hkv;
   a.dh = dh;
   a.scale_log2 = 1.4426950408889634f / std::sqrt((float)dh);
-  if (prefill_attn_launch(a, st) != hipSuccess) return HXF_EDEVICE;
-  return dev_rc(hipStreamSynchronize(st));
+  const bool ok = prefill_attn_launch(a, st) == hipSuccess;
+  const hipError_t done = hipStreamSynchronize(st);
+  return ok ? dev_rc(done) : HXF_EDEVICE;
 }
 
 int hxf_op_argmax(const float* logits, int32_t* out, int32_t R, int32_t V, void* stream) {

@@ -236,3 +236,19 @@ def test_prefill_plan_few_items_cut_to_the_share(p0, n):
     ([17, 0, 3000], [2300, 5, 640], 4, 2)])
 def test_prefill_plan_covers_every_key_tile_once(pos0, n, hq, hkv):
     _check_prefill(pos0, n, hq, hkv)
+
+
+@pytest.mark.parametrize("hq,hkv", [(32, 8), (64, 8), (4, 2)])
+def test_plan_of_forks_whose_common_pages_end_at_different_points(hq, hkv):
+    """Groups in scattered sequence order whose members leave the parent's pages after 1, 7 or all
+    of them, or share the first page only; batches of other sizes planned in between (the planner
+    keeps its working memory)."""
+    rng = np.random.default_rng(hq)
+    for n in (23, 3, 40, 1):
+        ctxs = [int(c) for c in rng.integers(130, 1500, n)]
+        bt = _tables(rng, ctxs)
+        order = rng.permutation(n)
+        for a in range(0, n - 3, 4):
+            for m, shared in zip(order[a + 1:a + 4], (int(rng.integers(1, 9)), 7, 8)):
+                bt[m, :shared] = bt[order[a], :shared]
+        _check(ctxs, hq, hkv, bt)
