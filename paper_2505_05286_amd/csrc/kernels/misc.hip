@@ -21,30 +21,37 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float* logits, int32
   const float* row = logits + (size_t)blockIdx.x * V;
   float bv = -__builtin_huge_valf();
   int bi = 0x7FFFFFFF;
+  // One workgroup per row: bound by the comparisons and the latency of its loads.  Four float4
+  // in flight per thread; a float4 first gives its maximum (NaN never wins a maximum), and only
+  // a larger one than all before replaces the thread's best, so equal values keep the lowest
+  // index (a thread's indices ascend).  The element is found in the best float4 at the end.
+  // 64 x 128256: 15.2 -> 9.9 us against comparing every element with its index, one row 13.5 -> 7.3.
   const int n4 = V >> 2;
   const float4* r4 = reinterpret_cast<const float4*>(row);
-  // four loads in flight per thread, then the comparisons (their order does not matter:
-  // better() breaks ties by index)
+  int b4 = -1;
+  auto top = [](const float4& v) { return fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)); };
+  auto take = [&](const float4& v, int j) __attribute__((always_inline)) {
+    const float t = top(v);
+    b4 = t > bv ? j : b4;
+    bv = fmaxf(bv, t);
+  };
   int i = threadIdx.x;
   for (; i + 3 * 1024 < n4; i += 4 * 1024) {
     float4 v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) v[u] = r4[i + u * 1024];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int j = 4 * (i + u * 1024);
-      better(bv, bi, v[u].x, j);
-      better(bv, bi, v[u].y, j + 1);
-      better(bv, bi, v[u].z, j + 2);
-      better(bv, bi, v[u].w, j + 3);
-    }
+    for (int u = 0; u < 4; ++u) take(v[u], i + u * 1024);
   }
-  for (; i < n4; i += 1024) {
-    const float4 v = r4[i];
-    better(bv, bi, v.x, 4 * i);
-    better(bv, bi, v.y, 4 * i + 1);
-    better(bv, bi, v.z, 4 * i + 2);
-    better(bv, bi, v.w, 4 * i + 3);
+  for (; i < n4; i += 1024) take(r4[i], i);
+  if (b4 >= 0) {
+    const float4 v = r4[b4];
+    bi = 4 * b4 + (v.x == bv ? 0 : v.y == bv ? 1 : v.z == bv ? 2 : 3);
+  } else {
+    // nothing above the type's lowest value: the first element that is not NaN
+    for (int j = 4 * threadIdx.x; j < 4 * n4 && bi == 0x7FFFFFFF; j += 4 * 1024)
+      for (int e = 3; e >= 0; --e)
+        if (row[j + e] == bv) bi = j + e;
   }
   for (int i = 4 * n4 + threadIdx.x; i < V; i += 1024) better(bv, bi, row[i], i);
 #pragma unroll

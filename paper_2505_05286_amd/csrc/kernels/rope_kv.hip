@@ -159,8 +159,11 @@ hipError_t rope_kv_partials_launch(uint16_t* qkv, const float* part, int S, cons
                                    int Hq, int Hkv, int dh, hipStream_t st) {
   if (T <= 0) return hipSuccess;
   if (dh > 128 || dh % 8) return hipErrorInvalidValue;
-  // prefill-sized batches without split partials write V through v_page_kernel
-  const bool v_pages = S == 0 && T >= 64 && (dh == 128 || dh == 64);
+  // Prefill-sized batches without split partials write V through v_page_kernel.  Up to 512 rows
+  // a second launch costs what it saves, and decode rows, each in a page of its own, gain nothing
+  // from it: 32 + 8 heads, in one kernel against two (us): 64 decode rows 3.0 / 2.6 + 3.9, 256
+  // 5.6 / 3.2 + 5.3; 256 prompt rows 5.0 / 3.2 + 2.6, 512 7.5 / 4.2 + 2.8, 1024 12.3 / 6.0 + 3.0.
+  const bool v_pages = S == 0 && T > 512 && (dh == 128 || dh == 64);
   const dim3 grid(T, ((v_pages ? Hq + Hkv : Hq + 2 * Hkv) + 3) / 4);
 #define HXF_ROPE(SS)                                                                                            \
   case SS:                                                                                                      \

@@ -297,6 +297,34 @@ def test_rope_kv_write(hq, hkv, dh):
     np.testing.assert_array_equal(flatv[slots], v)
 
 
+@pytest.mark.parametrize("hq,hkv,dh", [(32, 8, 128), (4, 2, 64)])
+@pytest.mark.parametrize("T", [511, 512, 513, 530])
+def test_rope_kv_write_around_the_page_kernel(hq, hkv, dh, T):
+    """Row counts on both sides of the switch to the kernel that writes V in whole page rows:
+    whole pages in order, then decode rows in pages of their own."""
+    t = torch()
+    rng = np.random.default_rng(hq + T)
+    nb, n_prompt = 600, T - 37
+    perm = rng.permutation(nb)
+    slots = np.array([perm[i // 16] * 16 + i % 16 for i in range(n_prompt)] +
+                     [perm[100 + i] * 16 + int(rng.integers(16)) for i in range(37)], np.int32)
+    qkvb, qkvf = rand_bf16(rng, (T, (hq + 2 * hkv) * dh))
+    pos = rng.integers(0, 3000, T).astype(np.int32)
+    table = t.empty(3000 * dh, dtype=t.float32, device="cuda:0")
+    hxf.op_rope_table(table.data_ptr(), 3000, dh, 10000.0)
+    qkv = dev_bits(qkvb)
+    kp, vp = _make_pools(nb, hkv, dh)
+    pos_d, slots_d = i32(pos), i32(slots)
+    hxf.op_rope_kv_write(qkv.data_ptr(), pos_d.data_ptr(), slots_d.data_ptr(), table.data_ptr(), kp.data_ptr(),
+                         vp.data_ptr(), nb, T, hq, hkv, dh)
+    t.cuda.synchronize()
+    K, V = _logical_pool(kp, vp, nb, hkv, dh)
+    k = qkvf[:, hq * dh:(hq + hkv) * dh].reshape(T, hkv, dh)
+    np.testing.assert_allclose(K.reshape(nb * 16, hkv, dh)[slots], M.apply_rope(k, pos, 1e4), rtol=2 ** -7, atol=2e-3)
+    np.testing.assert_array_equal(V.reshape(nb * 16, hkv, dh)[slots], qkvf[:, (hq + hkv) * dh:].reshape(T, hkv, dh))
+    assert not V.reshape(nb * 16, hkv, dh)[np.setdiff1d(np.arange(nb * 16), slots)].any()
+
+
 @pytest.mark.parametrize("hq,hkv,dh", [(32, 8, 128), (4, 2, 64), (40, 8, 128)])
 def test_rope_kv_write_prefill_rows(hq, hkv, dh):
     """A prefill-sized batch (V rows staged per 16 tokens and written as whole page rows):
@@ -527,6 +555,33 @@ def test_argmax_ties_and_lowest_index():
     hxf.op_argmax(xs.data_ptr(), out.data_ptr(), R, V)
     t.cuda.synchronize()
     np.testing.assert_array_equal(out.cpu().numpy(), M.argmax_lowest(x))
+
+
+@pytest.mark.parametrize("V", [4, 8, 4096, 4100, 16384, 20484])
+def test_argmax_special_values(V):
+    """NaN never wins, the lowest of equal values does (inside a group of four, across groups, a
+    thread's later groups and threads; 0 and -0 are equal), and a row of the lowest value alone
+    gives its first element that is not NaN."""
+    t = torch()
+    rng = np.random.default_rng(V)
+    x = rng.standard_normal((8, V)).astype(np.float32)
+    x[0, V // 2 + 1:] = x[0, V // 2]
+    x[0, : V // 2] = -5.0
+    x[1] = -np.inf
+    x[2] = -np.inf
+    x[2, 0:V:2] = np.nan
+    x[3] = np.nan
+    x[4, V - 3:] = np.inf
+    x[5, 1::3] = np.nan
+    x[6] = np.where(np.arange(V) % 3 == 1, 0.0, -0.0)
+    x[7, V - 1] = 9.0
+    x[7, V - 2] = np.nan
+    want = [0 if np.isnan(r).all() else int(np.flatnonzero(r == np.nanmax(r))[0]) for r in x]
+    out = t.empty(8, dtype=t.int32, device="cuda:0")
+    xs = t.from_numpy(x).to("cuda:0")
+    hxf.op_argmax(xs.data_ptr(), out.data_ptr(), 8, V)
+    t.cuda.synchronize()
+    np.testing.assert_array_equal(out.cpu().numpy(), want)
 
 
 def test_copy_probe():
