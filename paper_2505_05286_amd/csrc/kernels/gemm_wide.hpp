@@ -90,10 +90,12 @@ __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
   const int a_step = a.a_packed ? 2048 : 128, a_first = (kb / 2) * a_step;   // bytes per stage (kb is even)
   auto issue_a = [&](int s, bf16_t* base) __attribute__((always_inline)) {
     const int ss = min(s, nst - 1);
-    const bool last = s == nst - 1, past = s >= nst;   // past the last stage: zeros
+    // past the last stage: zeros.  Out of range by or-ing (kOutOfRange is the sign bit): as conditions
+    // these became branches that cut the loop into blocks, and the 8-wavefront tile spilled in it
+    const int past = s >= nst ? kOutOfRange : 0, last = s == nst - 1 ? kOutOfRange : 0;
 #pragma unroll
     for (int u = 0; u < A_PW; ++u)
-      buf_dma16(ra, past || (last && !a_in[u]) ? kOutOfRange : a_off[u], a_first + ss * a_step, base + a_dst[u]);
+      buf_dma16(ra, a_off[u] | past | (a_in[u] ? 0 : last), a_first + ss * a_step, base + a_dst[u]);
   };
   // weights: the wavefront's NW column tiles, for SwiGLU NW / 2 of the gate and the same NW / 2 of
   // the up matrix (tiles past N: zeros, or the last one again)
@@ -109,10 +111,10 @@ __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
   uint4 fb[R][NW];
   auto load_b = [&](auto rc, int k) __attribute__((always_inline)) {
     constexpr int r = decltype(rc)::value % R;
-    const int kk = kb + min(k, kt - 1);
+    const int kk = kb + min(k, kt - 1), past = k < kt ? 0 : kOutOfRange;
 #pragma unroll
     for (int j = 0; j < NW; ++j)   // past the last step: zeros
-      fb[r][j] = buf_load16<CACHE>(j < HALF ? rb0 : rb1, k < kt ? b_off[j % HALF] : kOutOfRange, kk * 1024);
+      fb[r][j] = buf_load16<CACHE>(j < HALF ? rb0 : rb1, b_off[j % HALF] | past, kk * 1024);
   };
   f32x4 acc[TM][NW];
 #pragma unroll
