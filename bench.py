@@ -342,7 +342,7 @@ def mixed_iteration_profile(dm, shape, n_profiled=3, n_warm=2, n_timed=8):
     pa = prof["prefill_attn_flops"] / (prof["prefill_attn_ms"] * 1e-3) / 1e12
     return {"bound": "mfma", "achieved": round(layer, 1), "peak": peak, "unit": "TFLOP/s",
             "frac": round(layer / peak, 4), "traffic": None,
-            "kernels": "gemm_big_kernel (QKV, O, gate/up + SwiGLU, down) of every layer",
+            "kernels": "gemm_wide_kernel (QKV, O, gate/up + SwiGLU, down) of every layer",
             "workload": "3: mixed iterations, 2048-token prefill chunk + 32 decode rows",
             "rows_per_iteration": rows, "iterations_profiled": iters,
             "ms_per_iteration_profiled": round(dt / iters * 1e3, 2),

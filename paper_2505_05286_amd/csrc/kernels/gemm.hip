@@ -162,8 +162,22 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu) {
   return p;
 }
 
-hipError_t gemm_launch(const GemmArgs& a, int epi, const GemmPlan& p, hipStream_t st, bool reduce, hipEvent_t e0,
+hipError_t gemm_launch(const GemmArgs& a, int epi, const GemmPlan& plan, hipStream_t st, bool reduce, hipEvent_t e0,
                        hipEvent_t e1) {
+  // A tile addresses its rows and its columns by 32-bit offsets: where a row pitch or a K in the
+  // millions makes either span 2 GiB, the smallest tile runs, whatever it costs.
+  GemmPlan p = plan;
+  auto fits = [&](int tm, int nw) {
+    const int64_t rows = std::min(16 * tm, a.M);
+    return (a.a_packed ? (rows + 15) / 16 * a.kt * 1024 : ((rows - 1) * a.lda + a.K) * 2) < (int64_t)1 << 31 &&
+           (int64_t)nw * a.kt * 1024 < (int64_t)1 << 31;
+  };
+  if (!fits(p.tm, p.nw)) {
+    p.tm = 1;
+    p.nw = 2;
+    p.wv = 4;
+    if (!fits(p.tm, p.nw)) return hipErrorInvalidValue;
+  }
   // packed activations in, or a packed SwiGLU output: K % 32 == 0 and F % 32 == 0
   if ((a.a_packed && (a.K % 32 || (epi == EPI_SWIGLU && a.N % 64 != 0))) ||
       (a.c_kt && (epi != EPI_SWIGLU || a.N % 64 != 0 || a.c_kt * 64 != a.N)))

@@ -557,6 +557,27 @@ def test_argmax_ties_and_lowest_index():
     np.testing.assert_array_equal(out.cpu().numpy(), M.argmax_lowest(x))
 
 
+@pytest.mark.parametrize("rows", [16, 17, 130, 200])
+def test_gemm_rows_spanning_more_than_32_bit_offsets(rows):
+    """A row pitch that puts a tile's rows more than 2 GiB apart gives the contiguous rows' result
+    (exactly: K = 64 is two MFMA steps in every tile)."""
+    t = torch()
+    N, K, lda = 64, 64, 8 << 20
+    a = t.empty((rows - 1) * lda + K, dtype=t.bfloat16, device="cuda:0")
+    view = a.as_strided((rows, K), (lda, 1))
+    dense = t.randn(rows, K, device="cuda:0").bfloat16()
+    view.copy_(dense)
+    rng = np.random.default_rng(rows)
+    w = dev_packed(rand_bf16(rng, (N, K))[0])
+    out = [t.empty(rows, N, dtype=t.float32, device="cuda:0") for _ in range(2)]
+    ws = t.empty(max(256, hxf.op_gemm_workspace_bytes(rows, N, K)), dtype=t.uint8, device="cuda:0")
+    for c, src, pitch in ((out[0], a, lda), (out[1], dense, K)):
+        hxf.op_gemm(src.data_ptr(), pitch, w.data_ptr(), 0, c.data_ptr(), N, rows, N, K, hxf.EPI_F32, ws.data_ptr(),
+                    ws.numel())
+    t.cuda.synchronize()
+    assert t.equal(out[0], out[1])
+
+
 @pytest.mark.parametrize("V", [4, 8, 4096, 4100, 16384, 20484])
 def test_argmax_special_values(V):
     """NaN never wins, the lowest of equal values does (inside a group of four, across groups, a
