@@ -557,6 +557,23 @@ def test_argmax_ties_and_lowest_index():
     np.testing.assert_array_equal(out.cpu().numpy(), M.argmax_lowest(x))
 
 
+@pytest.mark.parametrize("N", [32768, 32896, 65536, 65664, 98304, 98432])
+@pytest.mark.parametrize("M_", [1, 32, 33])
+def test_gemm_wide_outputs_around_the_tile_width_switch(M_, N):
+    """Few rows, outputs on both sides of where 128 columns per workgroup give way to 256: products
+    of small integers, exact in every order."""
+    t = torch()
+    K = 96
+    rng = np.random.default_rng(N + M_)
+    a, b = (rng.integers(-4, 5, s).astype(np.float32) for s in ((M_, K), (N, K)))
+    bits = lambda x: (x.view(np.uint32) >> 16).astype(np.uint16)
+    A, B = dev_bits(bits(a)), dev_packed(bits(b))
+    C = t.full((M_, N), float("nan"), dtype=t.float32, device="cuda:0")
+    hxf.op_gemm(A.data_ptr(), K, B.data_ptr(), 0, C.data_ptr(), N, M_, N, K, hxf.EPI_F32, 0, 0)
+    t.cuda.synchronize()
+    np.testing.assert_array_equal(C.cpu().numpy(), a @ b.T)
+
+
 @pytest.mark.parametrize("rows", [16, 17, 130, 200])
 def test_gemm_rows_spanning_more_than_32_bit_offsets(rows):
     """A row pitch that puts a tile's rows more than 2 GiB apart gives the contiguous rows' result
