@@ -54,6 +54,11 @@ int64_t hxf_op_gemm_workspace_bytes(int32_t M, int32_t N, int32_t K);
 int hxf_op_gemm(const void* A, int32_t lda, const void* B, const void* B2, void* C, int32_t ldc, int32_t M, int32_t N,
                 int32_t K, int32_t epilogue, void* workspace, int64_t workspace_bytes, void* stream);
 
+/* Introspection (host only, no device work): the tile and K split hxf_op_gemm takes for these sizes:
+ * plan = {row tiles of 16, column tiles of 16 per wavefront, wavefronts, 1 if the weights are fetched
+ * as read once, pieces of K, K per piece}. */
+int hxf_op_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t plan[6]);
+
 /* hxf_op_gemm without a workspace, for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid it).
  * Same arguments and result as hxf_op_gemm (the layout flags are refused: HXF_EINVAL);

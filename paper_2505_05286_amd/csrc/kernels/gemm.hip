@@ -74,27 +74,39 @@ __global__ __launch_bounds__(256) void pack_weight_kernel(const bf16_t* __restri
   *reinterpret_cast<uint4*>(out + q * 8) = v;
 }
 
-// Estimated time (us) of the wide kernel with 16 tm x 64 wv tiles and K cut into pieces of
-// k_chunk, above 128 rows.  Fitted to 5,900 measured launches (13 projection shapes of d
-// 4096-8192, 129-2300 rows, every tile height and split; weights not in the caches; 8% rms
-// error): a step of 32 of K takes the longest of the matrix pipe's issue time, its
-// power-limited time (which grows with the CUs at work) and, with several rows of tiles, the
-// time a CU needs to fetch its weights; workgroups run in rounds of one per CU; the weights
-// come at 5.4 TB/s at best where one row of tiles reads them (non-temporal loads), else at
-// 4.1; fp32 partials cost 0.22 us per MB written and 0.2 read back.
-double wide_time(int M, int N, int K, int tm, int wv, int k_chunk) {
-  const int tiles_m = (M + 16 * tm - 1) / (16 * tm), tiles_n = (N + 64 * wv - 1) / (64 * wv);
+// Estimated time (us) of the wide kernel above 128 rows with tiles of 16 tm x 16 nw wv and K cut
+// into pieces of k_chunk: a step of 32 of K takes the longest of the matrix pipe's issue time,
+// its power-limited time (which grows with the CUs at work) and the time a CU needs to fetch its
+// weights (by rows of tiles: the more of them, the more often a line is already in L2);
+// workgroups run in rounds of one per CU; the weights come at tb_s at best; fp32 partials cost
+// part_us per MB, written and read back.
+//
+// Fitted to launches with weights that are not in the caches: 64 (or 128) columns per
+// wavefront to 5,900 (13 projection shapes of d 4096-8192, 129-2300 rows), 32 columns to 10,600
+// (24 shapes, 129-2300 rows).  It only ranks: over the 28,700 launches of the second sweep its
+// error is 18 and 12% rms, 11 and 14% among the launches within a tenth of the best of their
+// shape, and the choice is 2.7% slower than the best tile on average, 22% at worst.
+struct TileCost {
+  double issue0, issue1, power0, power1, fetch[4], start, tb_s_once, tb_s, part_us;
+};
+constexpr TileCost kCols64{0.136, 0.0304, 0.0665, 0.0475, {0, 0.385, 0.337, 0.312}, 1.1, 5.4, 4.1, 0.42};
+constexpr TileCost kCols32{0.0816, 0.0222, 0.0245, 0.0204, {0.0714, 0.207, 0.164, 0.102}, 1.02, 5.0, 4.61, 0.592};
+
+double wide_time(int M, int N, int K, int tm, int nw, int wv, int k_chunk) {
+  const TileCost& c = nw == 2 ? kCols32 : kCols64;
+  const int tiles_m = (M + 16 * tm - 1) / (16 * tm), tiles_n = (N + 16 * nw * wv - 1) / (16 * nw * wv);
   const int splits = (K + k_chunk - 1) / k_chunk;
   const int wgs = tiles_m * tiles_n * splits;
   const double eff = (wv == 8 ? 1.75 : 1.0) * (tm == 16 ? 1.044 : 1.0);
   const double steps = k_chunk / 32.0;
-  const double fetch = tiles_m == 1 ? 0.0 : tiles_m == 2 ? 0.385 : tiles_m == 3 ? 0.337 : 0.312;
+  const double fetch = c.fetch[std::min(tiles_m, 4) - 1];
   auto round = [&](int n) {
-    return steps * std::max({(0.136 + 0.0304 * tm) * eff, (0.0665 + 0.0475 * tm) * eff * n / 256.0, fetch}) + 1.1;
+    return steps * std::max({(c.issue0 + c.issue1 * tm) * eff, (c.power0 + c.power1 * tm) * eff * n / 256.0, fetch}) +
+           c.start;
   };
   double t = wgs / 256 * round(256) + (wgs % 256 ? round(wgs % 256) : 0.0);
-  t = std::max(t, (double)N * K * 2e-6 / (tiles_m == 1 ? 5.4 : 4.1));
-  return t + (splits > 1 ? 0.42e-6 * splits * ((M + 15) / 16 * 16) * (double)N * 4 : 0.0);
+  t = std::max(t, (double)N * K * 2e-6 / (tiles_m == 1 ? c.tb_s_once : c.tb_s));
+  return t + (splits > 1 ? c.part_us * 1e-6 * splits * ((M + 15) / 16 * 16) * (double)N * 4 : 0.0);
 }
 
 }  // namespace
@@ -118,18 +130,23 @@ hipError_t pack_weight_launch(const uint16_t* W, int N, int K, uint16_t* out, hi
 //    271 at 32, 282 against 277 at 48; one row of 80000 x 4096 103 against 119, of 70000 x 8192 193
 //    against 221; where the shares are equal 256 are as good or better, 100000 x 4096 127 against 138).  These kernels replaced one that
 //    moved the weights through LDS: 94.6, 198 and 43.3 us.
-//  - Above, tile and split minimise the estimate.  Up to 512 rows K may be split (the partials
+//  - Above, tile and split minimise the estimate, over 64 and 32 columns per wavefront: 256-column
+//    workgroups leave outputs of a few thousand columns on a part of the chip with long K (down
+//    projections, row-major or packed alike), where half the width doubles the workgroups.
+//    4096 x 14336: 513 rows 141 us in 64 x 256 tiles, 92 in 96 x 128; 1024 rows 158 and 121; 240 rows
+//    52 (four pieces of K) and 44 (four pieces); 5120 x 27648 at 513 rows 276 and 171.  SwiGLU outputs are wide
+//    and stay with 64 columns.  Up to 512 rows K may be split (the partials
 //    of more rows cost more than the split gains); not for wide outputs, which fill the chip,
 //    nor for SwiGLU.  Partials outgrow the array of the allocation-free entry point only where
 //    they buy much (a million outputs or more, pieces of 2048 of K), so that the shapes it
 //    serves do not hang on small gains.
-// SwiGLU of a width that is no multiple of 32 has no 4-tile form (2 gate and 2 up tiles): 128
-// columns per workgroup at any row count.
+// SwiGLU of a width that is no multiple of 32 has no 64-column form (2 gate and 2 up tiles): 32
+// columns per wavefront at any row count.
 GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu) {
   GemmPlan p;
   const int row_tiles = (M + 15) / 16;
   const bool pairs_only = swiglu && N % 64 != 0;
-  if (row_tiles <= 8 || pairs_only) {
+  if (row_tiles <= 8) {
     const int tiles = (N + 127) / 128;
     p.once = true;
     // the fullest CU's share of the columns, in 128s, with either width
@@ -137,7 +154,7 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu) {
     p.nw = tiles <= 256 || pairs_only || (row_tiles <= 2 && 7 * busy4 >= 8 * busy2) ? 2 : 4;
     p.tm = row_tiles <= 1 ? 1 : row_tiles <= 2 ? 2 : row_tiles <= 4 ? 4 : p.nw == 4 && row_tiles <= 6 ? 6 : 8;
     int s = 1;
-    if (p.nw == 2 && row_tiles <= 8)
+    if (p.nw == 2)
       while (s + 1 <= max_splits && tiles * (s + 1) <= 256 && K / (s + 1) >= 512) ++s;
     p.k_chunk = ((K + s - 1) / s + 63) / 64 * 64;
     p.splits = (K + p.k_chunk - 1) / p.k_chunk;
@@ -145,25 +162,32 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu) {
   }
   const int most = M <= 512 && N < 16384 && !swiglu ? max_splits : 1;
   double best = 0;
-  auto consider = [&](int tm, int wv, int s) {
+  auto consider = [&](int tm, int nw, int wv, int s) {
     const int kc = ((K + s - 1) / s + 63) / 64 * 64;
-    const double t = wide_time(M, N, K, tm, wv, kc);
+    const double t = wide_time(M, N, K, tm, nw, wv, kc);
     if (best != 0 && t >= best) return;
     best = t;
     p.tm = tm;
+    p.nw = nw;
     p.wv = wv;
-    p.once = row_tiles <= tm;
+    p.once = nw == 4 && row_tiles <= tm;
     p.k_chunk = kc;
     p.splits = (K + kc - 1) / kc;
   };
-  for (int tm = 4; tm <= 16; ++tm) {
-    if (row_tiles <= tm && (tm % 2 || row_tiles + 2 <= tm)) continue;   // one row of tiles: the next even height
+  auto consider_splits = [&](int tm, int nw) {
     for (int s = 1; s <= most && (s == 1 || K / s >= 512); ++s)
-      if (s == 1 || (K / s >= 2048 && (int64_t)M * N >= 1 << 20) ||
+      if (s == 1 || (nw == 4 && K / s >= 2048 && (int64_t)M * N >= 1 << 20) ||
           (int64_t)s * row_tiles * 16 * N * 4 <= kNoallocPartials)
-        consider(tm, 4, s);
+        consider(tm, nw, 4, s);
+  };
+  if (!pairs_only) {
+    for (int tm = 4; tm <= 16; ++tm)
+      if (row_tiles > tm || (tm % 2 == 0 && row_tiles + 2 > tm)) consider_splits(tm, 4);   // one row of tiles: the next even height
+    if (M > 512) consider(9, 4, 8, 1);
   }
-  if (M > 512) consider(9, 8, 1);
+  if (!swiglu || pairs_only)
+    for (int tm = 3; tm <= 12; ++tm)
+      if (row_tiles + 1 > tm) consider_splits(tm, 2);   // one row of tiles: the height itself
   return p;
 }
 
@@ -181,6 +205,7 @@ hipError_t gemm_launch(const GemmArgs& a, int epi, const GemmPlan& plan, hipStre
     p.tm = 1;
     p.nw = 2;
     p.wv = 4;
+    p.once = true;
     if (!fits(p.tm, p.nw)) return hipErrorInvalidValue;
   }
   // packed activations in, or a packed SwiGLU output: K % 32 == 0 and F % 32 == 0

@@ -8,8 +8,8 @@ namespace hxf {
 namespace {
 
 // Macro tiles of 16 TM rows x 16 NW WV columns on the 16x16x32 MFMA: WV wavefronts, each
-// owning all the tile's rows and 16 NW of its columns (NW = 4, or 2 for the few rows of a
-// decode step, where narrow tiles fill the chip).  The weights go straight
+// owning all the tile's rows and 16 NW of its columns (NW = 4, or 2 where narrow tiles fill the
+// chip: the few rows of a decode step, or more rows of an output of a few thousand columns).  The weights go straight
 // from memory to registers (a wavefront's columns are its own, so nothing is read twice in a
 // workgroup; a packed tile is one contiguous kilobyte per load), R steps of 32 of K ahead;
 // only the activations pass through LDS, stages of 64 of K by buffer DMA, NS in flight.
@@ -26,6 +26,11 @@ namespace {
 // scheme are 5% slower, 8 steps of weights ahead 5-7%, 2 steps 2-4%, two workgroups per CU of
 // half the rows 5-10%.  With 8 wavefronts (144 rows x 512 columns, two per SIMD) 8192 x 28672
 // takes 847 us against 927 in the best tile of 4: 240 tiles, one round of the chip.
+//
+// NW = 2 above 128 rows: an A fragment feeds two MFMAs instead of four, but a workgroup fetches half
+// the weights per step, which is what bounds it there (16 KB per 0.31 us and CU with 64 x 256 tiles),
+// and there are twice as many.  4096 x 14336 at 513 rows: 160 workgroups of 96 x 128 in 92 us, 144
+// of 64 x 256 in 141; both operands through LDS took 108.
 //
 // Up to 128 rows the bytes of the weights are the bound: non-temporal loads where one row of
 // tiles reads them (55296 x 5120 at 64 rows 101.4 -> 93.0 us, 128256 x 4096 201 -> 182), and
@@ -275,17 +280,28 @@ template <int EPI, bool SPLIT>
 hipError_t launch_wide_cfg(const GemmArgs& a, const GemmPlan& p, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
 #define HXF_WIDE(T, NW, WV, CACHE) \
   case T: return launch_wide<T, NW, WV, CACHE, EPI, SPLIT>(a, p, st, e0, e1);
-  if (p.wv == 8) switch (p.tm) { HXF_WIDE(9, 4, 8, 0) }
-  else if (p.nw == 2) switch (p.tm) { HXF_WIDE(1, 2, 4, 2) HXF_WIDE(2, 2, 4, 2) HXF_WIDE(4, 2, 4, 2) HXF_WIDE(8, 2, 4, 2) }
-  else if (p.once) switch (p.tm) {
-      HXF_WIDE(1, 4, 4, 2) HXF_WIDE(2, 4, 4, 2) HXF_WIDE(4, 4, 4, 2) HXF_WIDE(6, 4, 4, 2) HXF_WIDE(8, 4, 4, 2)
+  if (p.nw == 2 && p.once) switch (p.tm) {
+      HXF_WIDE(1, 2, 4, 2) HXF_WIDE(2, 2, 4, 2) HXF_WIDE(4, 2, 4, 2) HXF_WIDE(8, 2, 4, 2)
+    }
+  else if (p.nw == 2) switch (p.tm) {
+      HXF_WIDE(3, 2, 4, 0) HXF_WIDE(4, 2, 4, 0) HXF_WIDE(5, 2, 4, 0) HXF_WIDE(6, 2, 4, 0) HXF_WIDE(7, 2, 4, 0)
+      HXF_WIDE(8, 2, 4, 0) HXF_WIDE(9, 2, 4, 0) HXF_WIDE(10, 2, 4, 0) HXF_WIDE(11, 2, 4, 0) HXF_WIDE(12, 2, 4, 0)
+    }
+  else if (p.wv == 4 && p.once) switch (p.tm) {
       HXF_WIDE(10, 4, 4, 2) HXF_WIDE(12, 4, 4, 2) HXF_WIDE(14, 4, 4, 2) HXF_WIDE(16, 4, 4, 2)
     }
-  else switch (p.tm) {
+  else if (p.wv == 4) switch (p.tm) {
       HXF_WIDE(4, 4, 4, 0) HXF_WIDE(5, 4, 4, 0) HXF_WIDE(6, 4, 4, 0) HXF_WIDE(7, 4, 4, 0) HXF_WIDE(8, 4, 4, 0)
       HXF_WIDE(9, 4, 4, 0) HXF_WIDE(10, 4, 4, 0) HXF_WIDE(11, 4, 4, 0) HXF_WIDE(12, 4, 4, 0) HXF_WIDE(13, 4, 4, 0)
       HXF_WIDE(14, 4, 4, 0) HXF_WIDE(15, 4, 4, 0) HXF_WIDE(16, 4, 4, 0)
     }
+  // few rows split K with 32 columns per wavefront only, eight wavefronts never do
+  if constexpr (!SPLIT) {
+    if (p.nw == 4 && p.wv == 4 && p.once) switch (p.tm) {
+        HXF_WIDE(1, 4, 4, 2) HXF_WIDE(2, 4, 4, 2) HXF_WIDE(4, 4, 4, 2) HXF_WIDE(6, 4, 4, 2) HXF_WIDE(8, 4, 4, 2)
+      }
+    if (p.nw == 4 && p.wv == 8) switch (p.tm) { HXF_WIDE(9, 4, 8, 0) }
+  }
 #undef HXF_WIDE
   return hipErrorInvalidValue;
 }

@@ -113,6 +113,14 @@ int64_t hxf_op_gemm_workspace_bytes(int32_t M, int32_t N, int32_t K) {
   return need;
 }
 
+int hxf_op_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t plan[6]) {
+  if (M <= 0 || N <= 0 || K <= 0 || epilogue < 0 || epilogue > 3 || !plan) return HXF_EINVAL;
+  const GemmPlan p = gemm_plan(M, N, K, 8, epilogue == HXF_EPI_SWIGLU);
+  const int32_t v[6] = {p.tm, p.nw, p.wv, p.once ? 1 : 0, p.splits, p.k_chunk};
+  std::copy(v, v + 6, plan);
+  return HXF_OK;
+}
+
 int hxf_op_gemm(const void* A, int32_t lda, const void* B, const void* B2, void* C, int32_t ldc, int32_t M, int32_t N,
                 int32_t K, int32_t flags, void* workspace, int64_t ws_bytes, void* stream) {
   const int epi = flags & 0xFF;

@@ -140,6 +140,7 @@ _SIGS = {
     "hxf_op_pack_weight": (C.c_int, [C.c_void_p, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p]),
     "hxf_op_gemm": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32,
                               C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p]),
+    "hxf_op_gemm_plan": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]),
     "hxf_op_gemm_noalloc": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32,
                                       C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_void_p]),
     "hxf_op_rmsnorm": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_float,
@@ -400,6 +401,13 @@ def _op(rc, what):
 
 def op_gemm_workspace_bytes(M, N, K):
     return lib().hxf_op_gemm_workspace_bytes(M, N, K)
+
+
+def op_gemm_plan(M, N, K, epi):
+    """{row tiles, column tiles per wavefront, wavefronts, read once, pieces of K, K per piece} of op_gemm."""
+    plan = (C.c_int32 * 6)()
+    _op(lib().hxf_op_gemm_plan(M, N, K, epi, plan), "hxf_op_gemm_plan")
+    return tuple(plan)
 
 
 def op_gemm(A, lda, B, B2, Cp, ldc, M, N, K, epi, ws=0, ws_bytes=0, stream=0):

@@ -1,0 +1,25 @@
+"""The GEMM's choice of tile and K split (host only): what the callers that size buffers from it
+rely on, and the choices whose alternatives were measured much slower."""
+import pytest
+
+from paper_2505_05286_amd import hxf
+
+
+@pytest.mark.parametrize("N,K,rows", [(4096, 14336, (176, 192, 208, 240, 256, 513, 600, 704, 768, 900, 1024)),
+                                      (5120, 27648, (176, 192, 513, 600, 704, 768, 900))])
+def test_down_projections_above_128_rows_take_128_columns(N, K, rows):
+    """A few thousand columns and long K: 256-column workgroups leave most of the chip idle
+    (513 rows of 4096 x 14336: 141 us against 92)."""
+    for M in rows:
+        tm, nw, wv = hxf.op_gemm_plan(M, N, K, hxf.EPI_RESID)[:3]
+        assert 16 * nw * wv == 128, (M, tm, nw, wv)
+
+
+@pytest.mark.parametrize("N", [256, 688, 2048, 4096, 5120, 7168, 10240, 16383])
+def test_partials_are_largest_at_the_last_row_of_a_row_tile(N):
+    """Buffers for every row count are sized at the multiples of 16 alone; above 512 rows K is whole."""
+    for K in (512, 2048, 4096, 8192, 11008, 14336, 28672):
+        for M16 in range(16, 513, 16):
+            full = hxf.op_gemm_workspace_bytes(M16, N, K)
+            assert all(hxf.op_gemm_workspace_bytes(M, N, K) <= full for M in (M16 - 15, M16 - 8, M16 - 1))
+        assert hxf.op_gemm_workspace_bytes(513, N, K) == hxf.op_gemm_workspace_bytes(2080, N, K) == 0
