@@ -125,11 +125,12 @@ hipError_t pack_weight_launch(const uint16_t* W, int N, int K, uint16_t* out, hi
 //    chip must be full: 128 columns per workgroup and K cut into the most pieces that stay
 //    within one workgroup per CU and >= 512 of K each; outputs of more than 256 such tiles
 //    take 256 columns unsplit (64 rows: 55296 x 5120 SwiGLU 91.6 us against 96.9, 128256 x 4096
-//    180 against 199; below, 28672 x 4096 41.8 against 55.6), except up to 32 rows where 128
-//    leave the fullest CU an eighth less to do (152064 x 5120: 225 against 242 at one row, 265 against
-//    271 at 32, 282 against 277 at 48; one row of 80000 x 4096 103 against 119, of 70000 x 8192 193
-//    against 221; where the shares are equal 256 are as good or better, 100000 x 4096 127 against 138).  These kernels replaced one that
-//    moved the weights through LDS: 94.6, 198 and 43.3 us.
+//    180 against 199; below, 28672 x 4096 41.8 against 55.6), except where 128 leave the fullest
+//    CU less to do: an eighth up to 32 rows (152064 x 5120: 225 against 242 at one row, 266 against
+//    271 at 32, 282 against 275 at 48), a quarter up to 64, where a narrow step also costs more
+//    (64 rows: 66048 x 8192 218 against 240, 70000 x 8192 223 / 245, 80000 x 4096 123 / 133; at 96
+//    rows of 80000 x 5120 173 / 171).  Where the shares are equal 256 are as good or better (one
+//    row of 100000 x 4096 125 against 138).  Both operands through LDS: 94.6, 198 and 43.3 us for the first three.
 //  - Above, tile and split minimise the estimate, over 64 and 32 columns per wavefront: 256-column
 //    workgroups leave outputs of a few thousand columns on a part of the chip with long K (down
 //    projections, row-major or packed alike), where half the width doubles the workgroups.
@@ -151,7 +152,8 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu) {
     p.once = true;
     // the fullest CU's share of the columns, in 128s, with either width
     const int busy2 = (tiles + 255) / 256, busy4 = 2 * (((N + 255) / 256 + 255) / 256);
-    p.nw = tiles <= 256 || pairs_only || (row_tiles <= 2 && 7 * busy4 >= 8 * busy2) ? 2 : 4;
+    const bool even_out = row_tiles <= 2 ? 7 * busy4 >= 8 * busy2 : row_tiles <= 4 && 3 * busy4 >= 4 * busy2;
+    p.nw = tiles <= 256 || pairs_only || even_out ? 2 : 4;
     p.tm = row_tiles <= 1 ? 1 : row_tiles <= 2 ? 2 : row_tiles <= 4 ? 4 : p.nw == 4 && row_tiles <= 6 ? 6 : 8;
     int s = 1;
     if (p.nw == 2)

@@ -23,3 +23,12 @@ def test_partials_are_largest_at_the_last_row_of_a_row_tile(N):
             full = hxf.op_gemm_workspace_bytes(M16, N, K)
             assert all(hxf.op_gemm_workspace_bytes(M, N, K) <= full for M in (M16 - 15, M16 - 8, M16 - 1))
         assert hxf.op_gemm_workspace_bytes(513, N, K) == hxf.op_gemm_workspace_bytes(2080, N, K) == 0
+
+
+@pytest.mark.parametrize("N,last", [(65664, 64), (66048, 64), (80000, 64), (98304, 64), (140000, 32), (152064, 32),
+                                    (200064, 32), (65536, 0), (98432, 0), (128256, 0), (256000, 0)])
+def test_wide_outputs_take_128_columns_where_256_leave_the_cus_uneven(N, last):
+    """Up to `last` rows: a quarter less for the fullest CU pays up to 64 rows, an eighth up to 32."""
+    for K in (2304, 8192):
+        for M in (1, 16, 32, 33, 40, 64, 65, 128):
+            assert hxf.op_gemm_plan(M, N, K, hxf.EPI_F32)[1] == (2 if M <= last else 4), M
