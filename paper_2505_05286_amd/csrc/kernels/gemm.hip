@@ -43,9 +43,61 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs a, int S) {
   else reinterpret_cast<float*>(a.C)[o] = s;
 }
 
+// The same product with 64-bit addresses and no LDS, for operands whose smallest tile (16 rows, 32
+// columns) spans 2 GiB: a wavefront owns 16 rows x 16 output columns (SwiGLU: and their gate and up
+// tiles) and reads both operands from memory.  split: grid.z cuts K as in the wide kernel.
+template <int EPI>
+__global__ __launch_bounds__(256) void gemm_far_kernel(GemmArgs a, int split) {
+  constexpr bool SW = EPI == EPI_SWIGLU;
+  const int lane = threadIdx.x & 63, n_out = SW ? a.N / 2 : a.N;
+  const int c0 = ((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6)) * 16, row = (int)blockIdx.y * 16 + (lane & 15);
+  if (c0 >= n_out) return;
+  const int64_t kb = split ? (int64_t)blockIdx.z * (a.k_chunk / 32) : 0;
+  const int64_t ke = split && kb + a.k_chunk / 32 < a.kt ? kb + a.k_chunk / 32 : a.kt;
+  const int r = min(row, a.M - 1);   // rows past M are never stored
+  const bf16_t* ap = a.a_packed ? a.A + (size_t)(r / 16) * a.kt * 512 + lane * 8 : a.A + (size_t)r * a.lda + (lane >> 4) * 8;
+  const bf16_t* bp = a.B + (size_t)(c0 / 16) * a.kt * 512 + lane * 8;
+  const bf16_t* up = SW ? a.B2 + (size_t)(c0 / 16) * a.kt * 512 + lane * 8 : nullptr;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f}, acc2 = acc;
+  for (int64_t k = kb; k < ke; ++k) {
+    uint4 x = make_uint4(0, 0, 0, 0);
+    if (a.a_packed || k * 32 + (lane >> 4) * 8 < a.K) x = load16(ap + k * (a.a_packed ? 512 : 32));
+    acc = mfma16x16x32(as_bf16x8(load16(bp + k * 512)), as_bf16x8(x), acc);
+    if constexpr (SW) acc2 = mfma16x16x32(as_bf16x8(load16(up + k * 512)), as_bf16x8(x), acc2);
+  }
+  if (row >= a.M) return;
+  // lane holds row l % 16 and columns 4 (l / 16) .. + 3
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int col = c0 + (lane >> 4) * 4 + e;
+    if (col >= n_out) continue;
+    const size_t o = (size_t)row * a.ldc + col;
+    if (split) {   // SwiGLU partials: logical columns in groups of 16 gate and 16 up
+      float* P = a.partial + ((size_t)blockIdx.z * a.M + row) * a.N;
+      P[SW ? (col >> 4) * 32 + (col & 15) : col] = acc[e];
+      if constexpr (SW) P[(col >> 4) * 32 + 16 + (col & 15)] = acc2[e];
+    } else if constexpr (SW) {
+      reinterpret_cast<bf16_t*>(a.C)[a.c_kt ? packed_elem(row, col, a.c_kt) : o] = f2bf(acc[e] / (1.f + __expf(-acc[e])) * acc2[e]);
+    } else if constexpr (EPI == EPI_BF16) {
+      reinterpret_cast<bf16_t*>(a.C)[o] = f2bf(acc[e]);
+    } else {
+      float* c = reinterpret_cast<float*>(a.C) + o;
+      *c = EPI == EPI_RESID ? *c + acc[e] : acc[e];
+    }
+  }
+}
+
 template <int EPI>
 hipError_t launch_epi(GemmArgs a, const GemmPlan& p, hipStream_t st, bool reduce, hipEvent_t e0, hipEvent_t e1) {
   a.k_chunk = p.k_chunk;
+  if (p.tm == 0) {   // no tile fits 32-bit offsets
+    const bool more = p.splits > 1 && reduce;
+    const dim3 grid(((EPI == EPI_SWIGLU ? a.N / 2 : a.N) + 63) / 64, (a.M + 15) / 16, p.splits);
+    hipError_t e = launch_ev(gemm_far_kernel<EPI>, grid, dim3(256), st, e0, more ? nullptr : e1, a, p.splits > 1 ? 1 : 0);
+    if (e != hipSuccess || !more) return e;
+    const size_t tot = (size_t)a.M * (EPI == EPI_SWIGLU ? a.N / 2 : a.N);
+    return launch_ev(splitk_reduce_kernel<EPI>, dim3((tot + 255) / 256), dim3(256), st, nullptr, e1, a, p.splits);
+  }
   if (p.splits > 1) {
     if (EPI != EPI_SWIGLU) a.B2 = nullptr;   // B2 marks SwiGLU there
     if (hipError_t e = gemm_wide_split(a, p, st, e0, reduce ? nullptr : e1)) return e;
@@ -195,8 +247,9 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu) {
 
 hipError_t gemm_launch(const GemmArgs& a, int epi, const GemmPlan& plan, hipStream_t st, bool reduce, hipEvent_t e0,
                        hipEvent_t e1) {
-  // A tile addresses its rows and its columns by 32-bit offsets: where a row pitch or a K in the
-  // millions makes either span 2 GiB, the smallest tile runs, whatever it costs.
+  // A tile addresses its rows and its columns by 32-bit offsets.  Where a row pitch or a K in the
+  // millions makes either span 2 GiB, the tallest tile that does not runs, and the 64-bit kernel
+  // where no tile does.
   GemmPlan p = plan;
   auto fits = [&](int tm, int nw) {
     const int64_t rows = std::min(16 * tm, a.M);
@@ -204,11 +257,20 @@ hipError_t gemm_launch(const GemmArgs& a, int epi, const GemmPlan& plan, hipStre
            (int64_t)nw * a.kt * 1024 < (int64_t)1 << 31;
   };
   if (!fits(p.tm, p.nw)) {
-    p.tm = 1;
-    p.nw = 2;
-    p.wv = 4;
-    p.once = true;
-    if (!fits(p.tm, p.nw)) return hipErrorInvalidValue;
+    const bool narrow = epi == EPI_SWIGLU && (p.splits > 1 || a.N % 64 != 0);   // no 64-column form
+    const GemmPlan was = p;
+    p.tm = 0;
+    for (int nw : {4, 2}) {
+      if (nw == 4 && (narrow || was.nw == 2)) continue;
+      for (int tm = std::min(was.tm, nw == 4 ? 16 : 12); p.tm == 0 && tm >= 1; --tm) {
+        const bool few = nw == 2 && (tm <= 2 || narrow);   // heights of the few-row form, 1, 2, 4 and 8
+        if ((tm < (nw == 4 ? 4 : 3) && !few) || (few && (tm > 8 || (tm & (tm - 1)))) || !fits(tm, nw)) continue;
+        p.tm = tm;
+        p.nw = nw;
+        p.wv = 4;
+        p.once = few;
+      }
+    }
   }
   // packed activations in, or a packed SwiGLU output: K % 32 == 0 and F % 32 == 0
   if ((a.a_packed && (a.K % 32 || (epi == EPI_SWIGLU && a.N % 64 != 0))) ||

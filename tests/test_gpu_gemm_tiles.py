@@ -110,3 +110,75 @@ def test_instances(kind, narrow, once):
                     t.testing.assert_close(out.double(), want, rtol=2 ** -8, atol=1e-30)
                 else:
                     assert t.equal(out, want)
+
+
+def _fits(rows, lda, K, tm):
+    return ((min(16 * tm, rows) - 1) * lda + K) * 2 < 1 << 31
+
+
+MI = 1 << 20
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,lda,N,K,kind,far", [
+    (64, 24 * MI, 64, 72, "f32", False), (65, 24 * MI, 64, 1032, "resid", False), (33, 40 * MI, 128, 1024, "swiglu", False),
+    (129, 16 * MI, 22016, 64, "bf16", False), (129, 16 * MI, 22016, 64, "swiglu", False),
+    (129, 24 * MI, 22016, 64, "swiglu", False), (150, 32 * MI, 1376, 256, "swiglu", False),
+    (17, 72 * MI, 500, 200, "f32", True), (18, 72 * MI, 64, 1032, "bf16", True), (17, 72 * MI, 64, 264, "resid", True),
+    (17, 72 * MI, 96, 264, "swiglu", True), (19, 72 * MI, 64, 2056, "swiglu", True)])
+def test_row_pitches_beyond_a_tile(rows, lda, N, K, kind, far):
+    """A row pitch that puts a planned tile's rows more than 2 GiB apart: a lower tile runs, or, where
+    16 rows still span 2 GiB, the kernel with 64-bit addresses; with and without split K."""
+    t = torch()
+    dev, epi = "cuda:0", EPI[kind]
+    assert not _fits(rows, lda, K, hxf.op_gemm_plan(rows, N, K, epi)[0]) and _fits(rows, lda, K, 1) != far
+    g = t.Generator(device=dev)
+    g.manual_seed(rows + N)
+    n_out = N // 2 if kind == "swiglu" else N
+    a = t.randint(-4, 5, (rows, K), generator=g, device=dev).to(t.bfloat16)
+    w = [t.randint(-4, 5, (n_out, K), generator=g, device=dev).to(t.bfloat16) for _ in range(2)]
+    wp = []
+    for x in w:
+        wp.append(t.zeros(hxf.packed_weight_bytes(n_out, K) // 2, dtype=t.bfloat16, device=dev))
+        hxf.op_pack_weight(x.data_ptr(), n_out, K, wp[-1].data_ptr())
+    far_apart = t.empty((rows - 1) * lda + K, dtype=t.bfloat16, device=dev)
+    far_apart.as_strided((rows, K), (lda, 1)).copy_(a)
+    out = t.ones((rows, n_out), dtype=t.float32 if kind in ("f32", "resid") else t.bfloat16, device=dev)
+    wsn = hxf.op_gemm_workspace_bytes(rows, N, K)
+    ws = t.empty(max(wsn, 256), dtype=t.uint8, device=dev)
+    log(f"pitch {rows} x {lda} N={N} K={K} {kind} ws={wsn}")
+    hxf.op_gemm(far_apart.data_ptr(), lda, wp[0].data_ptr(), wp[1].data_ptr() if kind == "swiglu" else 0,
+                out.data_ptr(), n_out, rows, N, K, epi, ws.data_ptr(), wsn)
+    t.cuda.synchronize()
+    prod = [a.float() @ x.float().T for x in w]
+    if kind == "swiglu":
+        d = [x.double() for x in prod]
+        t.testing.assert_close(out.double(), d[0] * t.sigmoid(d[0]) * d[1], rtol=2 ** -8, atol=1e-30)
+    else:
+        assert t.equal(out, {"f32": prod[0], "resid": prod[0] + 1, "bf16": prod[0].bfloat16()}[kind])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("packed", [False, True])
+def test_rows_of_more_than_2_gib_of_weights(packed):
+    """K so long that the two column tiles of the narrowest form span 2 GiB: split K on 64-bit addresses."""
+    t = torch()
+    dev, M, N, K = "cuda:0", 2, 16, 34 * MI
+    at = t.tensor([0, 7, 63, 1000, 4194303, 4194304, 12345678, K // 2 + 5, K - 9, K - 1], device=dev)
+    a = t.zeros((M, K), dtype=t.bfloat16, device=dev)
+    w = t.zeros((N, K), dtype=t.bfloat16, device=dev)
+    a[:, at] = t.randint(1, 5, (M, len(at)), device=dev).to(t.bfloat16)
+    w[:, at] = t.randint(1, 5, (N, len(at)), device=dev).to(t.bfloat16)
+    src = a
+    wp = t.zeros(hxf.packed_weight_bytes(N, K) // 2, dtype=t.bfloat16, device=dev)
+    hxf.op_pack_weight(w.data_ptr(), N, K, wp.data_ptr())
+    if packed:
+        src = t.zeros(hxf.packed_weight_bytes(M, K) // 2, dtype=t.bfloat16, device=dev)
+        hxf.op_pack_weight(a.data_ptr(), M, K, src.data_ptr())
+    out = t.zeros((M, N), dtype=t.float32, device=dev)
+    ws = t.empty(hxf.op_gemm_workspace_bytes(M, N, K), dtype=t.uint8, device=dev)
+    log(f"long K, packed={packed}, plan {hxf.op_gemm_plan(M, N, K, hxf.EPI_F32)}")
+    hxf.op_gemm(src.data_ptr(), K, wp.data_ptr(), 0, out.data_ptr(), N, M, N, K,
+                hxf.EPI_F32 | (hxf.GEMM_A_PACKED if packed else 0), ws.data_ptr(), ws.numel())
+    t.cuda.synchronize()
+    assert t.equal(out, a[:, at].float() @ w[:, at].float().T)
