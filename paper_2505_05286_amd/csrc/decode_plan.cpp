@@ -49,9 +49,11 @@ void plan_decode_streams(const std::vector<DecodeSeq>& seqs, int hkv, int G, Dec
       for (int k = i + 1; k < j && s > 0; ++k) {
         const DecodeSeq& m = seqs[(uint32_t)order[k]];
         s = std::min(s, m.ctx / kPage);
-        if (std::memcmp(m.pages, lead.pages, (size_t)s * sizeof(int32_t)) == 0) continue;
-        int c = 0;
-        while (m.pages[c] == lead.pages[c]) ++c;   // ends before s: the runs differ
+        // as memory inside both tables; a context longer than its table reads no further than the
+        // first difference
+        const int whole = std::min({s, m.n_pages, lead.n_pages});
+        int c = std::memcmp(m.pages, lead.pages, (size_t)whole * sizeof(int32_t)) == 0 ? whole : 0;
+        while (c < s && m.pages[c] == lead.pages[c]) ++c;
         s = c;
       }
       if (s > 0) {
@@ -107,10 +109,13 @@ void plan_decode_streams(const std::vector<DecodeSeq>& seqs, int hkv, int G, Dec
   }
   out.n_parts = slot;
   // Launch order: one-tile items, then the wide ones, each longest first, so that the
-  // wavefronts that start last, when the chip drains, are the short pieces.
-  std::stable_sort(out.runs.begin(), out.runs.end(), [&](const DecodePlan::Run& x, const DecodePlan::Run& y) {
+  // wavefronts that start last, when the chip drains, are the short pieces; equal lengths in
+  // stream order.
+  std::sort(out.runs.begin(), out.runs.end(), [&](const DecodePlan::Run& x, const DecodePlan::Run& y) {
     const bool wx = streams[x.stream].n_rows > R1, wy = streams[y.stream].n_rows > R1;
-    return wx != wy ? wy : x.len > y.len;
+    if (wx != wy) return wy;
+    if (x.len != y.len) return x.len > y.len;
+    return x.stream != y.stream ? x.stream < y.stream : x.piece0 < y.piece0;
   });
 }
 

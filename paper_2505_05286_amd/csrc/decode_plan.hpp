@@ -16,6 +16,7 @@ struct DecodeSeq {
   int entry;
   int ctx;
   const int32_t* pages;
+  int n_pages = 1 << 30;   // entries of the table, where ctx may exceed it (a plan alone may be asked for)
 };
 
 struct DecodePlan {

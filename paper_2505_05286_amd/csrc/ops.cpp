@@ -75,7 +75,7 @@ AttnHost& attn_host() {
 void decode_seqs(int B, const int32_t* ctx, const int32_t* bt_host, int bt_stride, std::vector<DecodeSeq>& seqs) {
   seqs.clear();
   for (int b = 0; b < B; ++b)
-    seqs.push_back(DecodeSeq{b, std::max(ctx[b], 1), bt_host ? bt_host + (size_t)b * bt_stride : nullptr});
+    seqs.push_back(DecodeSeq{b, std::max(ctx[b], 1), bt_host ? bt_host + (size_t)b * bt_stride : nullptr, bt_stride});
 }
 
 DecodeLayout decode_layout(const DecodePlan& P, int B, int Hq, int Hkv, int dh) {

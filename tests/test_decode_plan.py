@@ -2,12 +2,18 @@
 attends to each of its context tokens exactly once, its partials fill a block of
 consecutive slots, shared-prefix items only cover pages the rows really share, and
 the items fill the resident wavefronts without exceeding them."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
 from paper_2505_05286_amd import hxf
 
 from ._lib import ensure_built
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 RESIDENT = 2048
 
@@ -252,3 +258,36 @@ def test_plan_of_forks_whose_common_pages_end_at_different_points(hq, hkv):
             for m, shared in zip(order[a + 1:a + 4], (int(rng.integers(1, 9)), 7, 8)):
                 bt[m, :shared] = bt[order[a], :shared]
         _check(ctxs, hq, hkv, bt)
+
+
+_GUARDED = """
+import ctypes, mmap, sys
+import numpy as np
+from paper_2505_05286_amd import hxf
+size = mmap.PAGESIZE
+area = mmap.mmap(-1, 2 * size)
+base = ctypes.addressof(ctypes.c_char.from_buffer(area))
+libc = ctypes.CDLL(None, use_errno=True)
+assert libc.mprotect(ctypes.c_void_p(base + size), size, 0) == 0
+rows = np.array([[5, 6, 7, 8], [5, 6, 9, 8]], np.int32)
+at = base + size - rows.nbytes                       # the table ends where nothing may be read
+ctypes.memmove(at, rows.ctypes.data, rows.nbytes)
+table, ctx = ctypes.cast(at, ctypes.POINTER(ctypes.c_int32)), (ctypes.c_int32 * 2)(16 * 900, 16 * 800)
+n_items, n_merges = ctypes.c_int32(), ctypes.c_int32()
+L = hxf.lib()
+assert L.hxf_op_decode_attention_workspace_bytes(2, 8, 2, 64, ctx, table, 4) > 0
+items, merges = np.zeros((4096, 24), np.int32), np.zeros((64, 4), np.int32)
+rc = L.hxf_op_decode_plan(2, 8, 2, ctx, table, 4, items.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), 4096,
+                          ctypes.byref(n_items), merges.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), 64,
+                          ctypes.byref(n_merges))
+shared = items[:n_items.value][items[:n_items.value, 3] > 1]
+assert rc == 0 and shared[:, 2].max() == 32, (rc, shared)
+print("planned")
+"""
+
+
+def test_plan_of_contexts_longer_than_their_table_rows():
+    """A plan may be asked for contexts beyond the table rows: nothing past the table is read once the
+    rows have differed (run in a child process: the page behind the table is not readable)."""
+    r = subprocess.run([sys.executable, "-c", _GUARDED], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "planned" in r.stdout, (r.returncode, r.stderr[-2000:])
