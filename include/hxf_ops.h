@@ -6,10 +6,12 @@
  * All pointers are DEVICE pointers unless marked "host".  bf16 tensors are
  * uint16 bit patterns.  Every call enqueues work on `stream` (hipStream_t, may
  * be 0) and returns HXF_OK (0) or a negative hxf error code; errors are not
- * sticky and leave nothing enqueued.  The caller owns every buffer.  Calls
+ * sticky and leave nothing enqueued.  The caller owns every device buffer.  Calls
  * that build a work list on the host (attention) copy it into the caller's
  * `workspace` with an asynchronous host-to-device copy and synchronise the
- * stream before returning, so their host arguments may be freed afterwards.
+ * stream before returning, so their host arguments may be freed afterwards; each
+ * thread that makes them keeps up to 4 MiB of pinned and 4 MiB of pageable host
+ * memory for it until the thread ends.
  *
  * Physical KV layout (one layer), kv-head major: K pool [Hkv][n_blocks][dh/8][16][8]
  * (element (token t, dim d) of a page at ((d/8)*16 + t)*8 + d%8), then a separate

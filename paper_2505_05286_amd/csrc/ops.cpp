@@ -27,8 +27,9 @@ struct DecodeLayout {
 // Host state of the attention calls, one per thread and kept between calls: the plans (whose
 // working memory is reused) and a pinned staging buffer for the work lists.  Every call waits
 // for its stream before it returns, so nothing reads the buffer afterwards, whatever stream
-// and device the next call uses.  Lists beyond kStageMax go through pageable memory, so that
-// the pinned memory a thread holds (until it ends) is bounded.
+// and device the next call uses.  Lists beyond kStageMax go through pageable memory, and a call
+// that leaves more than kStageMax in the plans and lists gives all of that back: a thread holds at
+// most 4 MiB pinned and 4 MiB pageable, until it ends.
 constexpr size_t kStageMax = size_t(4) << 20;
 // Decode lists up to this size go through pageable memory too: the runtime copies those itself, with
 // no transfer to wait for (a call with a list of 0.8-4 KB takes 1.2-2.3 us less than from pinned
@@ -66,11 +67,32 @@ struct AttnHost {
     pageable.resize(bytes);
     return pageable.data();
   }
+  template <typename... T>
+  static size_t held(const std::vector<T>&... v) {
+    return (... + (v.capacity() * sizeof(T)));
+  }
+  void give_back() {
+    if (held(decode.items, decode.merges, decode.streams, decode.runs, decode.order, decode.members, decode.shared,
+             decode.slots, decode.base, prefill.items, prefill.merges, seqs, entries, pageable) <= kStageMax)
+      return;
+    decode = DecodePlan();
+    prefill = PrefillPlan();
+    seqs = std::vector<DecodeSeq>();
+    entries = std::vector<PrefillEntry>();
+    pageable = std::vector<uint8_t>();
+  }
 };
-AttnHost& attn_host() {
-  static thread_local AttnHost h;
-  return h;
-}
+// The thread's state for one call
+struct AttnUse {
+  AttnHost& h;
+  AttnUse() : h(thread_state()) {}
+  ~AttnUse() { h.give_back(); }
+  AttnUse(const AttnUse&) = delete;
+  static AttnHost& thread_state() {
+    static thread_local AttnHost state;
+    return state;
+  }
+};
 
 void decode_seqs(int B, const int32_t* ctx, const int32_t* bt_host, int bt_stride, std::vector<DecodeSeq>& seqs) {
   seqs.clear();
@@ -208,7 +230,8 @@ int hxf_op_kv_scatter(const void* k, const void* v, const int32_t* slot, void* k
 int64_t hxf_op_decode_attention_workspace_bytes(int32_t B, int32_t Hq, int32_t Hkv, int32_t dh, const int32_t* ctx,
                                                 const int32_t* bt_host, int32_t bt_stride) {
   if (B < 0 || !ctx || !shapes_ok(Hq, Hkv, dh) || (bt_host && bt_stride <= 0)) return -1;
-  AttnHost& H = attn_host();
+  const AttnUse use;
+  AttnHost& H = use.h;
   decode_seqs(B, ctx, bt_host, bt_stride, H.seqs);
   DecodePlan& P = H.decode;
   plan_decode_streams(H.seqs, Hkv, Hq / Hkv, P);
@@ -221,7 +244,8 @@ int hxf_op_decode_plan(int32_t B, int32_t Hq, int32_t Hkv, const int32_t* ctx, c
   if (B < 0 || !ctx || Hq <= 0 || Hkv <= 0 || Hq % Hkv || Hq / Hkv > 16 || (bt_host && bt_stride <= 0) || !n_items ||
       !n_merges || (items_cap > 0 && !items) || (merges_cap > 0 && !merges))
     return HXF_EINVAL;
-  AttnHost& H = attn_host();
+  const AttnUse use;
+  AttnHost& H = use.h;
   decode_seqs(B, ctx, bt_host, bt_stride, H.seqs);
   DecodePlan& P = H.decode;
   plan_decode_streams(H.seqs, Hkv, Hq / Hkv, P);
@@ -241,7 +265,8 @@ int hxf_op_decode_attention(const void* q, const void* k_pool, const void* v_poo
   if (B == 0) return HXF_OK;
   for (int b = 0; b < B; ++b)
     if (ctx[b] <= 0 || (ctx[b] + kPage - 1) / kPage > bt_stride) return HXF_EINVAL;
-  AttnHost& H = attn_host();
+  const AttnUse use;
+  AttnHost& H = use.h;
   decode_seqs(B, ctx, bt_host, bt_stride, H.seqs);
   DecodePlan& P = H.decode;
   plan_decode_streams(H.seqs, Hkv, Hq / Hkv, P);
@@ -327,13 +352,14 @@ int hxf_op_prefill_plan(int32_t S, int32_t Hq, int32_t Hkv, const int32_t* pos0,
   if (S < 0 || Hq <= 0 || Hkv <= 0 || Hq % Hkv || Hq / Hkv > 16 || (S > 0 && (!pos0 || !n_host)) || !n_items ||
       !n_merges || (items_cap > 0 && !items) || (merges_cap > 0 && !merges))
     return HXF_EINVAL;
-  std::vector<PrefillEntry>& entries = attn_host().entries;
+  const AttnUse use;
+  std::vector<PrefillEntry>& entries = use.h.entries;
   entries.clear();
   for (int s = 0; s < S; ++s) {
     if (n_host[s] < 0 || pos0[s] < 0) return HXF_EINVAL;
     if (n_host[s] > 0) entries.push_back(PrefillEntry{s, pos0[s], n_host[s]});
   }
-  PrefillPlan& P = attn_host().prefill;
+  PrefillPlan& P = use.h.prefill;
   plan_prefill(entries, Hkv, prefill_queries_per_item(Hq / Hkv), P);
   *n_items = (int32_t)P.items.size();
   *n_merges = (int32_t)P.merges.size();
@@ -358,7 +384,8 @@ int hxf_op_prefill_attention(const void* q, const void* k_pool, const void* v_po
   const int64_t need = hxf_op_prefill_attention_workspace_bytes(S, Hq, Hkv, n_host);
   if (!workspace || ws_bytes < need) return HXF_ENOMEM;
   const int qpi = prefill_queries_per_item(Hq / Hkv);
-  AttnHost& H = attn_host();
+  const AttnUse use;
+  AttnHost& H = use.h;
   H.entries.clear();
   for (int s = 0; s < S; ++s)
     if (n_host[s] > 0) H.entries.push_back(PrefillEntry{s, pos0[s], n_host[s]});

@@ -291,3 +291,36 @@ def test_plan_of_contexts_longer_than_their_table_rows():
     rows have differed (run in a child process: the page behind the table is not readable)."""
     r = subprocess.run([sys.executable, "-c", _GUARDED], cwd=ROOT, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "planned" in r.stdout, (r.returncode, r.stderr[-2000:])
+
+
+_LARGE = """
+import ctypes as C, sys
+import numpy as np
+from paper_2505_05286_amd import hxf
+def resident_mib():
+    return int(open("/proc/self/statm").read().split()[1]) * 4096 / 2 ** 20
+n = 400_000
+ctx, ones = np.full(n, 300, np.int32), np.ones(n, np.int32)
+P = C.POINTER(C.c_int32)
+n_items, n_merges, none = C.c_int32(), C.c_int32(), None
+L = hxf.lib()
+before = resident_mib()
+if sys.argv[1] == "decode":
+    rc = L.hxf_op_decode_plan(n, 32, 8, ctx.ctypes.data_as(P), none, 0, none, 0, C.byref(n_items), none, 0,
+                              C.byref(n_merges))
+else:
+    rc = L.hxf_op_prefill_plan(n, 32, 8, ctx.ctypes.data_as(P), ones.ctypes.data_as(P), none, 0, C.byref(n_items),
+                               none, 0, C.byref(n_merges))
+assert rc == hxf.ENOMEM and n_items.value > 2 * n, (rc, n_items)
+held = resident_mib() - before
+assert held < 56, f"{held:.0f} MiB held after the call"
+print("given back")
+"""
+
+
+@pytest.mark.parametrize("which", ["decode", "prefill"])
+def test_a_large_plan_is_given_back(which):
+    """The thread's plans are kept between calls up to 4 MiB only (the plan of 400,000 sequences takes
+    over 70 MiB)."""
+    r = subprocess.run([sys.executable, "-c", _LARGE, which], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "given back" in r.stdout, (r.returncode, r.stderr[-2000:])
