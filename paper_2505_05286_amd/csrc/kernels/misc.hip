@@ -21,18 +21,24 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float* logits, int32
   const float* row = logits + (size_t)blockIdx.x * V;
   float bv = -__builtin_huge_valf();
   int bi = 0x7FFFFFFF;
-  // One workgroup per row: bound by the comparisons and the latency of its loads.  Four float4
-  // in flight per thread; a float4 first gives its maximum (NaN never wins a maximum), and only
-  // a larger one than all before replaces the thread's best, so equal values keep the lowest
-  // index (a thread's indices ascend).  The element is found in the best float4 at the end.
-  // 64 x 128256: 15.2 -> 9.9 us against comparing every element with its index, one row 13.5 -> 7.3.
+  // One workgroup per row: bound by the comparisons and the latency of its loads, from 200 rows on by
+  // memory.  Four float4 in flight per thread; a float4 first gives its maximum (NaN never wins a
+  // maximum), and only a larger one than all before replaces the thread's best, so equal values
+  // keep the lowest index (a thread's indices ascend).  The best float4 stays in registers and
+  // its element is found at the end (reading it again cost a dependent load, and at many rows its
+  // traffic: 256 x 128256 26.1 -> 24.5 us, 128 rows 14.2 -> 12.8, 64 rows 10.6 -> 9.8; against comparing
+  // every element with its index 24.4, 17.0 and 16.1, one row 13.9 -> 7.3).
   const int n4 = V >> 2;
   const float4* r4 = reinterpret_cast<const float4*>(row);
   int b4 = -1;
-  auto top = [](const float4& v) { return fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)); };
+  float4 best = make_float4(0.f, 0.f, 0.f, 0.f);
   auto take = [&](const float4& v, int j) __attribute__((always_inline)) {
-    const float t = top(v);
-    b4 = t > bv ? j : b4;
+    const float t = fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w));
+    const bool up = t > bv;
+    b4 = up ? j : b4;
+    best.x = up ? v.x : best.x;
+    best.y = up ? v.y : best.y;
+    best.z = up ? v.z : best.z;
     bv = fmaxf(bv, t);
   };
   int i = threadIdx.x;
@@ -45,8 +51,7 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float* logits, int32
   }
   for (; i < n4; i += 1024) take(r4[i], i);
   if (b4 >= 0) {
-    const float4 v = r4[b4];
-    bi = 4 * b4 + (v.x == bv ? 0 : v.y == bv ? 1 : v.z == bv ? 2 : 3);
+    bi = 4 * b4 + (best.x == bv ? 0 : best.y == bv ? 1 : best.z == bv ? 2 : 3);
   } else {
     // nothing above the type's lowest value: the first element that is not NaN
     for (int j = 4 * threadIdx.x; j < 4 * n4 && bi == 0x7FFFFFFF; j += 4 * 1024)
