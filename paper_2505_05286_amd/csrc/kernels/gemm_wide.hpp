@@ -46,7 +46,12 @@ namespace {
 // SPLIT: grid.y cuts K into chunks of k_chunk (a multiple of 64); each writes its fp32
 // partial [M][N] to slot blockIdx.y of a.partial (SwiGLU: with NW = 2, logical columns in
 // groups of 16 gate and 16 up).
-template <int TM, int NW, int R, int EPI, bool SPLIT, int WV, int OCC, int CACHE>
+// SHORT: K of at most 256 with one row of tiles: all of it is requested at once and multiplied after one
+// wait, because the pipeline's start and end (a wait and a barrier per 64 of K, steps over zeros)
+// are a tenth of such a call: 1, 2 and 16 rows of 512 x 256 2.65 / 3.4 / 3.6 us against 3.1 / 3.9 / 4.0,
+// 1376 x 256 SwiGLU 3.7 / 3.9 / 3.8 against 4.2 / 4.4 / 4.2.  (As a branch of the same kernel it made K = 688 0.3 us
+// slower; from 33 rows on it gains nothing.)
+template <int TM, int NW, int R, int EPI, bool SPLIT, int WV, int OCC, int CACHE, bool SHORT>
 __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
   constexpr int BM = 16 * TM, BN = 16 * NW * WV, NS = 4;
   constexpr int A_BLK = TM * 2, A_PW = (A_BLK + WV - 1) / WV, STAGE = A_BLK * 512;   // 1 KB blocks per stage, per wavefront
@@ -67,7 +72,7 @@ __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
   };
   const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
   const int L = xcd_remap(blockIdx.x, tiles_m * tiles_n);
-  const int tn = L / tiles_m, tm = L % tiles_m;
+  const int tn = SHORT ? L : L / tiles_m, tm = SHORT ? 0 : L % tiles_m;
   const int m0 = tm * BM, n0 = tn * BN;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kb = SPLIT ? blockIdx.y * (a.k_chunk / 32) : 0;              // first step (32 of K)
@@ -150,6 +155,27 @@ __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);    // one LDS read
     });
   };
+  if constexpr (SHORT) {
+    static_assert(R == 2 * NS && !SPLIT, "a ring slot per step, a stage per slot");
+    static_for<R>([&](auto ic) { load_b(ic, decltype(ic)::value); });
+    static_for<NS>([&](auto ic) { issue_a(decltype(ic)::value, slot(ic)); });   // past the last: zeros, as the weights
+    wait_vmcnt<0>();
+    __builtin_amdgcn_s_barrier();
+    static_for<NS>([&](auto ic) {
+      bf16x8 f[2][TM];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) f[h][i] = read_a(slot(ic), i, h);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < NW; ++j)
+            acc[i][j] = mfma16x16x32(as_bf16x8(fb[2 * decltype(ic)::value + h][j]), f[h][i], acc[i][j]);
+    });
+  } else {
   static_for<NS - 1>([&](auto ic) {
     issue_a(decltype(ic)::value, slot(ic));
     __builtin_amdgcn_sched_barrier(0);   // the waits below count in this order
@@ -205,6 +231,7 @@ __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
     load_b(std::integral_constant<int, 0>{}, k + R);
   }
   wait_vmcnt<0>();
+  }
 
   // lane holds row l % 16 and columns 4 (l / 16) .. + 3 of each 16 x 16 tile
   const int col4 = (lane >> 4) * 4;
@@ -268,11 +295,11 @@ __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
 
 // Shapes: 16 tm rows x 16 nw wv columns.  Weights that one row of tiles reads (tiles_m == 1) are
 // fetched with the non-temporal hint (p.once).
-template <int TM, int NW, int WV, int CACHE, int EPI, bool SPLIT>
+template <int TM, int NW, int WV, int CACHE, int EPI, bool SPLIT, bool SHORT = false>
 hipError_t launch_wide(const GemmArgs& a, const GemmPlan& p, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   constexpr int BM = 16 * TM, BN = 16 * NW * WV, R = WV == 8 ? 2 : NW == 2 ? 8 : 4, OCC = WV / 4;
   const int nb = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  return launch_ev(gemm_wide_kernel<TM, NW, R, EPI, SPLIT, WV, OCC, CACHE>, dim3(nb, p.splits), dim3(64 * WV), st, e0,
+  return launch_ev(gemm_wide_kernel<TM, NW, R, EPI, SPLIT, WV, OCC, CACHE, SHORT>, dim3(nb, p.splits), dim3(64 * WV), st, e0,
                    e1, a);
 }
 
@@ -280,6 +307,12 @@ template <int EPI, bool SPLIT>
 hipError_t launch_wide_cfg(const GemmArgs& a, const GemmPlan& p, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
 #define HXF_WIDE(T, NW, WV, CACHE) \
   case T: return launch_wide<T, NW, WV, CACHE, EPI, SPLIT>(a, p, st, e0, e1);
+  if constexpr (!SPLIT) {
+    if (p.nw == 2 && p.once && a.kt <= 8 && a.M <= 16 * p.tm) {
+      if (p.tm == 1) return launch_wide<1, 2, 4, 2, EPI, false, true>(a, p, st, e0, e1);
+      if (p.tm == 2) return launch_wide<2, 2, 4, 2, EPI, false, true>(a, p, st, e0, e1);
+    }
+  }
   if (p.nw == 2 && p.once) switch (p.tm) {
       HXF_WIDE(1, 2, 4, 2) HXF_WIDE(2, 2, 4, 2) HXF_WIDE(4, 2, 4, 2) HXF_WIDE(8, 2, 4, 2)
     }
