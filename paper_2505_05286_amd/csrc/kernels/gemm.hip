@@ -175,7 +175,7 @@ hipError_t pack_weight_launch(const uint16_t* W, int N, int K, uint16_t* out, hi
 // Tile and split-K choice; everything depends on M through its 16-row tiles only.
 //  - Up to 128 rows one row of tiles covers M and the weights' bytes are the bound, so the
 //    chip must be full: 128 columns per workgroup and K cut into the most pieces that stay
-//    within one workgroup per CU and >= 512 of K each; outputs of more than 256 such tiles
+//    within one workgroup per CU and >= 512 of K each, and shorten the pipeline; outputs of more than 256 such tiles
 //    take 256 columns unsplit (64 rows: 55296 x 5120 SwiGLU 91.6 us against 96.9, 128256 x 4096
 //    180 against 199; below, 28672 x 4096 41.8 against 55.6), except where 128 leave the fullest
 //    CU less to do: an eighth up to 32 rows (152064 x 5120: 225 against 242 at one row, 266 against
@@ -210,6 +210,15 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu) {
     int s = 1;
     if (p.nw == 2)
       while (s + 1 <= max_splits && tiles * (s + 1) <= 256 && K / (s + 1) >= 512) ++s;
+    // The pipeline runs 1 + 8 n steps of 32 of K, and one or two steps left over singly, which wait
+    // for all their loads and cost about a trip of eight: a cut that saves no trip only adds partials
+    // (one row of 6144 x 4096 in five pieces 13.6 us, in four 13.2; 64 rows 18.7 and 18.0; 5120 x 5120 in six
+    // and five 14.2 and 13.8, 64 rows 20.1 and 18.9; of 40 such shapes measured the worst loses 2%).
+    auto steps = [&](int pieces) {
+      const int n = std::min(((K + pieces - 1) / pieces + 63) / 64 * 2, (K + 31) / 32), trips = (n + 4) / 8;
+      return 1 + 8 * trips + 8 * std::max(n - 1 - 8 * trips, 0);
+    };
+    while (s > 1 && steps(s - 1) <= steps(s)) --s;
     p.k_chunk = ((K + s - 1) / s + 63) / 64 * 64;
     p.splits = (K + p.k_chunk - 1) / p.k_chunk;
     return p;

@@ -32,3 +32,11 @@ def test_wide_outputs_take_128_columns_where_256_leave_the_cus_uneven(N, last):
     for K in (2304, 8192):
         for M in (1, 16, 32, 33, 40, 64, 65, 128):
             assert hxf.op_gemm_plan(M, N, K, hxf.EPI_F32)[1] == (2 if M <= last else 4), M
+
+
+@pytest.mark.parametrize("N,K,pieces", [(6144, 4096, 4), (5120, 5120, 5), (6144, 3072, 4), (4096, 14336, 8), (7168, 5120, 4),
+                                        (4096, 4096, 8), (2048, 8192, 8), (256, 688, 1)])
+def test_few_rows_cut_k_only_where_a_piece_runs_fewer_trips(N, K, pieces):
+    for M in (1, 17, 64, 128):
+        *_, s, k = hxf.op_gemm_plan(M, N, K, hxf.EPI_BF16)
+        assert s == pieces and k % 64 == 0 and (s - 1) * k < K <= s * k, (M, s, k)
