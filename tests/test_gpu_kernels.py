@@ -91,9 +91,8 @@ def test_gemm_swiglu(M_, N, K):
                                     (1, 128, 40), (17, 130, 552), (33, 2050, 1096), (128, 33000, 136), (90, 40000, 64)])
 @pytest.mark.parametrize("epi", [hxf.EPI_BF16, hxf.EPI_RESID])
 def test_gemm_wide_tile_edges(M_, N, K, epi):
-    """Every tile height of the register-weight kernel (a row count just inside it), outputs whose
-    rows are no multiple of four columns (element stores), K that ends inside a stage, a step or the
-    first step, split and unsplit, and the eight-wavefront shape.  The activation rows are longer
+    """Outputs whose rows are no multiple of four columns (element stores), K that ends inside a stage, a
+    step or the first step, split and unsplit, low tiles and the eight-wavefront shape.  The activation rows are longer
     than K and hold NaN past it: nothing beyond K may reach a product.  One activation is infinite:
     steps run over zeros past K must not turn its row's infinities into NaN."""
     t = torch()
@@ -325,20 +324,25 @@ def test_rope_kv_write_around_the_page_kernel(hq, hkv, dh, T):
     assert not V.reshape(nb * 16, hkv, dh)[np.setdiff1d(np.arange(nb * 16), slots)].any()
 
 
+@pytest.mark.parametrize("n_whole", [12, 34])
 @pytest.mark.parametrize("hq,hkv,dh", [(32, 8, 128), (4, 2, 64), (40, 8, 128)])
-def test_rope_kv_write_prefill_rows(hq, hkv, dh):
-    """A prefill-sized batch (V rows staged per 16 tokens and written as whole page rows):
-    12 whole pages in order, 32 tokens from the middle of a page on, a 16-token group whose
-    slots run in order but start mid-page, then 90 tokens in scattered slots."""
+def test_rope_kv_write_prefill_rows(hq, hkv, dh, n_whole):
+    """A prompt's rows, 330 in one kernel and 682 with V staged per 16 tokens and written as whole
+    page rows: whole pages in order, 32 tokens from the middle of a page on, a 16-token group whose
+    slots run in order but start mid-page (two pages that are neighbours in the pool), then 90
+    tokens in scattered slots."""
     t = torch()
     rng = np.random.default_rng(7 * hq + dh)
     nb, maxpos = 80, 9000
     perm = rng.permutation(nb)
-    whole = [int(b) * 16 + j for b in perm[:12] for j in range(16)]
-    mid = [int(perm[12]) * 16 + 5 + j for j in range(11)] + [int(perm[13]) * 16 + j for j in range(16)] + \
-          [int(perm[14]) * 16 + j for j in range(5)]
-    shifted = [int(perm[15]) * 16 + 3 + j for j in range(13)] + [int(perm[16]) * 16 + j for j in range(3)]
-    free = np.array([int(b) * 16 + j for b in perm[17:] for j in range(16)])
+    pair = int(rng.integers(nb - 1))
+    perm = perm[(perm != pair) & (perm != pair + 1)]
+    whole = [int(b) * 16 + j for b in perm[:n_whole] for j in range(16)]
+    perm = perm[n_whole:]
+    mid = [int(perm[0]) * 16 + 5 + j for j in range(11)] + [int(perm[1]) * 16 + j for j in range(16)] + \
+          [int(perm[2]) * 16 + j for j in range(5)]
+    shifted = [pair * 16 + 3 + j for j in range(16)]
+    free = np.array([int(b) * 16 + j for b in perm[3:] for j in range(16)])
     rest = [int(x) for x in rng.permutation(free)[:90]]
     slots = np.array(whole + mid + shifted + rest, np.int32)
     assert len(set(slots.tolist())) == len(slots)
@@ -576,8 +580,8 @@ def test_gemm_wide_outputs_around_the_tile_width_switch(M_, N):
 
 @pytest.mark.parametrize("rows", [16, 17, 130, 200])
 def test_gemm_rows_spanning_more_than_32_bit_offsets(rows):
-    """A row pitch that puts a tile's rows more than 2 GiB apart gives the contiguous rows' result
-    (exactly: K = 64 is two MFMA steps in every tile)."""
+    """Rows of 16 MiB pitch (a planned tile spans up to 1 GiB, all rows more than 32-bit offsets) give the
+    contiguous rows' result (exactly: K = 64 is two MFMA steps in every tile)."""
     t = torch()
     N, K, lda = 64, 64, 8 << 20
     a = t.empty((rows - 1) * lda + K, dtype=t.bfloat16, device="cuda:0")
@@ -620,6 +624,28 @@ def test_argmax_special_values(V):
     hxf.op_argmax(xs.data_ptr(), out.data_ptr(), 8, V)
     t.cuda.synchronize()
     np.testing.assert_array_equal(out.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("M_", [5, 40, 100, 300, 700])
+@pytest.mark.parametrize("pitch,start", [(0, 0), (4, 0), (2, 0), (1, 0), (0, 4), (0, 2), (0, 1), (1, 1), (3, 3)])
+def test_gemm_rows_at_any_pitch_and_start(M_, pitch, start):
+    """Activations whose row pitch or first row is no multiple of 16 (or 4) bytes: any lda >= K is
+    taken.  Products of small integers, exact in every order; NaN between the rows."""
+    t = torch()
+    N, K = 256, 200
+    rng = np.random.default_rng(M_ + 10 * pitch + start)
+    a, b = (rng.integers(-4, 5, s).astype(np.float32) for s in ((M_, K), (N, K)))
+    bits = lambda x: (x.view(np.uint32) >> 16).astype(np.uint16)
+    lda = K + pitch
+    flat = np.full(start + M_ * lda + 64, 0x7FC0, np.uint16)
+    flat[start:start + M_ * lda].reshape(M_, lda)[:, :K] = bits(a)
+    A, B = dev_bits(flat), dev_packed(bits(b))
+    ws = t.empty(max(256, hxf.op_gemm_workspace_bytes(M_, N, K)), dtype=t.uint8, device="cuda:0")
+    C = t.full((M_, N), float("nan"), dtype=t.float32, device="cuda:0")
+    hxf.op_gemm(A.data_ptr() + 2 * start, lda, B.data_ptr(), 0, C.data_ptr(), N, M_, N, K, hxf.EPI_F32, ws.data_ptr(),
+                ws.numel())
+    t.cuda.synchronize()
+    np.testing.assert_array_equal(C.cpu().numpy(), a @ b.T)
 
 
 def test_copy_probe():
