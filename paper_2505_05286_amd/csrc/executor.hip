@@ -88,7 +88,7 @@ WsPlan plan_workspace(const hxf_model_cfg& m, const hxf_sched_cfg& s) {
                              words(p.pf_merges_max * (int64_t)(sizeof(PrefillMerge) / 4));
   p.meta_bytes = meta_words * 4;
   // split-K partials: largest splits*M*N over the GEMM shapes at M <= 512 (no plan
-  // splits K above 512 rows; a plan depends on M through its 16-row tiles only)
+  // splits K above 512 rows, and the last row count of a 16-row tile has the largest partials)
   int64_t part = 0;
   const int64_t shapes[5][3] = {{qkv, d, 0}, {d, hq * dh, 0}, {2 * f, d, 1}, {d, f, 0}, {m.vocab, d, 0}};
   for (int64_t M = 16; M < std::min<int64_t>(512, p.t_max) + 16; M += 16)

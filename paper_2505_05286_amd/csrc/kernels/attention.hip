@@ -325,13 +325,14 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeAttnArgs a) {
 // v_pos), so the V^T operand of a lane is one contiguous 16-byte LDS read.  Softmax is
 // online in log2 units, one exchange of the wavefront halves per tile for the max.
 //
-// A step multiplies K of tile t + 1 and V of tile t, so that the scores of the next tile and
-// the exponentials of this one run side by side in a wavefront; the tiles come by buffer DMA,
-// whose count leaves the LDS reads their own (with global_load_lds every LDS wait was a full
-// one).  What bounds it: LDS reads (each wavefront reads every K and V byte for its 32 pairs,
-// 1 KB per MFMA), exponentials and MFMAs each take 40-50% of a step, and the two wavefronts
-// of a SIMD overlap them only in part.  2048 queries at position 0 / 2048 / 6144: 54.9 / 112.4
-// / 252 us -> 54.2 / 108.7 / 233 (1.03 PFLOP/s).  The order of interleave() against the
+// A step multiplies K of tile t + 1 and V of tile t, so that the scores of the next tile and the
+// exponentials of this one run side by side in a wavefront; the tiles come by buffer DMA, whose count
+// leaves the LDS reads their own (with global_load_lds every LDS wait was a full one).  What bounds
+// it: no one unit.  At 6144 the matrix pipes are busy 53% of the cycles, the LDS ports 26% (each
+// wavefront reads every K and V byte for its 32 pairs), a wavefront issues VALU work in 28% of its
+// cycles and waits in 19% (28% before), and the clock has fallen to 1.9 GHz; at 0, where the diagonal
+// and the start of an item weigh more, 26, 13, 25 and 22%.  2048 queries at position 0 / 2048 / 6144:
+// 54.9 / 112.4 / 252 us -> 53.8 / 107.5 / 231 (1.04 PFLOP/s).  The order of interleave() against the
 // compiler's own: 54.6 / 109.0 / 237.
 template <int DH>
 __global__ __launch_bounds__(256) void prefill_flash_kernel(PrefillAttnArgs a) {

@@ -72,9 +72,10 @@ __device__ __forceinline__ T wave_max(T v) {
 // ---- LDS DMA: each lane moves 16 bytes from its own address to lds_block + 16 * lane,
 // without passing through registers; completion is counted by vmcnt.  It goes through a
 // buffer descriptor (MUBUF), because a global_load_lds is a FLAT instruction to the compiler:
-// while one is in flight it can only wait for every LDS read and every load at once.  Buffer accesses are counted exactly, so LDS reads and
-// loads stay in flight across the uses of older ones; their address is a 32-bit lane offset
-// plus a scalar offset (no 64-bit VALU adds), and a lane offset at or past `bytes` reads zeros.
+// while one is in flight it can only wait for every LDS read and every load at once.  Buffer
+// accesses are counted exactly, so LDS reads and loads stay in flight across the uses of older
+// ones; their address is a 32-bit lane offset plus a scalar offset (no 64-bit VALU adds), and a
+// lane offset at or past `bytes` reads zeros (and writes them to LDS).  Addresses need no alignment.
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 constexpr int kOutOfRange = (int)0x80000000u;   // a lane offset past every buffer

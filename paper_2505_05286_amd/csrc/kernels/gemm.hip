@@ -172,29 +172,32 @@ hipError_t pack_weight_launch(const uint16_t* W, int N, int K, uint16_t* out, hi
   return hipGetLastError();
 }
 
-// Tile and split-K choice; everything depends on M through its 16-row tiles only.
-//  - Up to 128 rows one row of tiles covers M and the weights' bytes are the bound, so the
-//    chip must be full: 128 columns per workgroup and K cut into the most pieces that stay
-//    within one workgroup per CU and >= 512 of K each, and shorten the pipeline; outputs of more than 256 such tiles
-//    take 256 columns unsplit (64 rows: 55296 x 5120 SwiGLU 91.6 us against 96.9, 128256 x 4096
-//    180 against 199; below, 28672 x 4096 41.8 against 55.6), except where 128 leave the fullest
-//    CU less to do: an eighth up to 32 rows (152064 x 5120: 225 against 242 at one row, 266 against
-//    271 at 32, 282 against 275 at 48), a quarter up to 64, where a narrow step also costs more
-//    (64 rows: 66048 x 8192 218 against 240, 70000 x 8192 223 / 245, 80000 x 4096 123 / 133; at 96
-//    rows of 80000 x 5120 173 / 171).  Where the shares are equal 256 are as good or better (one
-//    row of 100000 x 4096 125 against 138).  Both operands through LDS: 94.6, 198 and 43.3 us for the first three.
+// Tile and split-K choice.  It depends on M through its 16-row tiles, and on M itself where the
+// partials may outgrow the allocation-free array (a million outputs): the fewer rows of a tile never
+// have larger partials than its sixteen.
+//  - Up to 128 rows one row of tiles covers M and the weights' bytes are the bound, so the chip must
+//    be full: 128 columns per workgroup and K cut into the most pieces that stay within one workgroup
+//    per CU and >= 512 of K each, and shorten the pipeline; outputs of more than 256 such tiles take
+//    256 columns unsplit (64 rows: 55296 x 5120 SwiGLU 91.6 us against 96.9, 128256 x 4096 180
+//    against 199; below, 28672 x 4096 41.8 against 55.6), except where 128 leave the fullest CU less
+//    to do: an eighth up to 32 rows (152064 x 5120: 225 against 242 at one row, 266 against 271 at
+//    32, 282 against 275 at 48), a quarter up to 64, where a narrow step also costs more (64 rows:
+//    66048 x 8192 218 against 240, 70000 x 8192 223 / 245, 80000 x 4096 123 / 133; at 96 rows of
+//    80000 x 5120 173 / 171).  Where the shares are equal 256 are as good or better (one row of
+//    100000 x 4096 125 against 138).  Both operands through LDS: 94.6, 198 and 43.3 us for the first
+//    three.
 //  - Above, tile and split minimise the estimate, over 64 and 32 columns per wavefront: 256-column
 //    workgroups leave outputs of a few thousand columns on a part of the chip with long K (down
-//    projections, row-major or packed alike), where half the width doubles the workgroups.
-//    4096 x 14336: 513 rows 141 us in 64 x 256 tiles, 92 in 96 x 128; 1024 rows 158 and 121; 240 rows
-//    52 (four pieces of K) and 44 (four pieces); 5120 x 27648 at 513 rows 276 and 171.  SwiGLU outputs are wide
-//    and stay with 64 columns.  Up to 512 rows K may be split (the partials
-//    of more rows cost more than the split gains); not for wide outputs, which fill the chip,
-//    nor for SwiGLU.  Partials outgrow the array of the allocation-free entry point only where
-//    they buy much (a million outputs or more, pieces of 2048 of K), so that the shapes it
-//    serves do not hang on small gains.
-// SwiGLU of a width that is no multiple of 32 has no 64-column form (2 gate and 2 up tiles): 32
-// columns per wavefront at any row count.
+//    projections, row-major or packed alike), where half the width doubles the workgroups. 4096 x
+//    14336: 513 rows 141 us in 64 x 256 tiles, 92 in 96 x 128; 1024 rows 158 and 121; 240 rows 52
+//    (four pieces of K) and 44 (four pieces); 5120 x 27648 at 513 rows 276 and 171.  SwiGLU outputs
+//    are wide and stay with 64 columns.  Up to 512 rows K may be split (the partials of more rows
+//    cost more than the split gains); not for wide outputs, which fill the chip, nor for SwiGLU.
+//    Partials outgrow the array of the allocation-free entry point only where they buy much (a
+//    million outputs or more, pieces of 2048 of K), so that the shapes it serves do not hang on small
+//    gains.
+// SwiGLU of a width that is no multiple of 32 has no 64-column form (2 gate and 2 up
+//    tiles): 32 columns per wavefront at any row count.
 GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu) {
   GemmPlan p;
   const int row_tiles = (M + 15) / 16;
@@ -212,8 +215,9 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu) {
       while (s + 1 <= max_splits && tiles * (s + 1) <= 256 && K / (s + 1) >= 512) ++s;
     // The pipeline runs 1 + 8 n steps of 32 of K, and one or two steps left over singly, which wait
     // for all their loads and cost about a trip of eight: a cut that saves no trip only adds partials
-    // (one row of 6144 x 4096 in five pieces 13.6 us, in four 13.2; 64 rows 18.7 and 18.0; 5120 x 5120 in six
-    // and five 14.2 and 13.8, 64 rows 20.1 and 18.9; of 40 such shapes measured the worst loses 2%).
+    // (one row of 6144 x 4096 in five pieces 13.6 us, in four 13.2; 64 rows 18.7 and 18.0; 5120 x
+    // 5120 in six and five 14.2 and 13.8, 64 rows 20.1 and 18.9; of 40 such shapes measured the worst
+    // loses 2%).
     auto steps = [&](int pieces) {
       const int n = std::min(((K + pieces - 1) / pieces + 63) / 64 * 2, (K + 31) / 32), trips = (n + 4) / 8;
       return 1 + 8 * trips + 8 * std::max(n - 1 - 8 * trips, 0);
@@ -246,6 +250,8 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu) {
   if (!pairs_only) {
     for (int tm = 4; tm <= 16; ++tm)
       if (row_tiles > tm || (tm % 2 == 0 && row_tiles + 2 > tm)) consider_splits(tm, 4);   // one row of tiles: the next even height
+    // (measured at 129-512 rows too: it wins only where two rows of 144 fit just so, 288 rows of
+    // 55296 x 5120 155 us against 174, and is even or slower elsewhere)
     if (M > 512) consider(9, 4, 8, 1);
   }
   if (!swiglu || pairs_only)

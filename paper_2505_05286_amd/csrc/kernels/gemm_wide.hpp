@@ -1,4 +1,5 @@
-// bf16 "NT" GEMM C[M,N] = A[M,K] * B[N,K]^T with the weights read straight into registers.  Instantiated by gemm_wide_*.hip, one epilogue each.
+// bf16 "NT" GEMM C[M,N] = A[M,K] * B[N,K]^T with the weights read straight into registers.
+// Instantiated by gemm_wide_*.hip, one epilogue each.
 #pragma once
 
 #include "gemm_util.hpp"
@@ -7,49 +8,56 @@ namespace hxf {
 
 namespace {
 
-// Macro tiles of 16 TM rows x 16 NW WV columns on the 16x16x32 MFMA: WV wavefronts, each
-// owning all the tile's rows and 16 NW of its columns (NW = 4, or 2 where narrow tiles fill the
-// chip: the few rows of a decode step, or more rows of an output of a few thousand columns).  The weights go straight
-// from memory to registers (a wavefront's columns are its own, so nothing is read twice in a
-// workgroup; a packed tile is one contiguous kilobyte per load), R steps of 32 of K ahead;
-// only the activations pass through LDS, stages of 64 of K by buffer DMA, NS in flight.
+// Macro tiles of 16 TM rows x 16 NW WV columns on the 16x16x32 MFMA: WV wavefronts, each owning all
+// the tile's rows and 16 NW of its columns (NW = 4, or 2 where narrow tiles fill the chip: the few
+// rows of a decode step, or more rows of an output of a few thousand columns).  The weights go
+// straight from memory to registers (a wavefront's columns are its own, so nothing is read twice in a
+// workgroup; a packed tile is one contiguous kilobyte per load), R steps of 32 of K ahead; only the
+// activations pass through LDS, stages of 64 of K by buffer DMA, NS in flight.
 //
-// Why: with both operands in LDS and 8 wavefronts the CU's LDS port (128 B/cycle) was the
-// bound: 192 x 256 tiles read 0.83 KB and wrote 0.29 KB per 32x32x16 MFMA, of the 1 KB per
-// MFMA the port has; here an A fragment feeds four MFMAs and only A is written (0.6 KB).  One
+// Why: with both operands staged in LDS by eight wavefronts (192 x 256 tiles, 1.1 KB through LDS per
+// 32x32x16 MFMA) the wavefronts spent 37-49% of their cycles waiting for those DMAs, with the matrix pipes
+// busy 31-52% and LDS reads 19-27% of the time.  Here the weights are requested R steps ahead of their
+// use and no barrier stands between, an A fragment feeds four MFMAs and only A is written (0.6 KB):
+// 12-28% of the cycles waiting, matrix pipes busy 38% (O) to 62% (gate/up) at a clock that falls from
+// 2.26 to 1.97 GHz as they get busier, LDS reads 10-16%.  One
 // wavefront per SIMD keeps the accumulators (4 TM registers x 4) in AGPRs and needs its own
 // overlap: the A fragments of step k + 1 are read into the registers that step k has just
 // used, one LDS read after every NW MFMAs, and the barrier of a stage lies half a stage
 // before its first use.  Measured (2080 rows, back to back, against 8 wavefronts with both
 // operands in LDS): 57344 x 8192 SwiGLU from row-major activations 1970 -> 1512 us
-// (1.29 PFLOP/s), 6144 x 4096 112 -> 89, 4096 x 14336 290 -> 227; 32x32x16 MFMAs on this
+// (1.29 PFLOP/s), 6144 x 4096 112 -> 89, 4096 x 14336 290 -> 219; 32x32x16 MFMAs on this
 // scheme are 5% slower, 8 steps of weights ahead 5-7%, 2 steps 2-4%, two workgroups per CU of
 // half the rows 5-10%.  With 8 wavefronts (144 rows x 512 columns, two per SIMD) 8192 x 28672
-// takes 847 us against 927 in the best tile of 4: 240 tiles, one round of the chip.
+// takes 847 us against 927 in the best tile of 4: 240 tiles, one round of the chip (three registers
+// spill in its loop).
 //
 // NW = 2 above 128 rows: an A fragment feeds two MFMAs instead of four, but a workgroup fetches half
 // the weights per step, which is what bounds it there (16 KB per 0.31 us and CU with 64 x 256 tiles),
 // and there are twice as many.  4096 x 14336 at 513 rows: 160 workgroups of 96 x 128 in 92 us, 144
 // of 64 x 256 in 141; both operands through LDS took 108.
 //
-// Up to 128 rows the bytes of the weights are the bound: non-temporal loads where one row of
-// tiles reads them (55296 x 5120 at 64 rows 101.4 -> 93.0 us, 128256 x 4096 201 -> 182), and
-// against a kernel with the weights in LDS: one row 37.5 -> 36.0 us (28672 x 4096) and 19.4 ->
-// 17.3 (4096 x 14336), 64 rows 44.5 -> 41.2 and 24.4 -> 24.0, 64 x 128256 x 4096 203 -> 182.
+// Up to 128 rows the bytes of the weights are the bound: non-temporal loads where one row of tiles
+// reads them (55296 x 5120 at 64 rows 101.4 -> 93.0 us, 128256 x 4096 201 -> 182; the first pass over
+// weights just written also waits for the memory-side cache to write back up to 256 MB of them,
+// 128256 x 8192 at 64 rows 410 us then and 333 after, whatever the order of the tiles), and against a
+// kernel with the weights in LDS: one row 37.5 -> 36.0 us (28672 x 4096) and 19.4 -> 17.3 (4096 x
+// 14336), 64 rows 44.5 -> 41.2 and 24.4 -> 24.0, 64 x 128256 x 4096 203 -> 182.
 //
-// Row-major activations are staged as 8 rows x 128 bytes per DMA (whole cache lines), with
-// the eight 16-byte chunks of row r stored in the order chunk ^ (r / 2 % 8), so that the 16
-// lanes of a fragment read touch 16 different 16-byte columns of LDS; packed activations are
-// 1 KB tiles in operand order already.  SwiGLU groups logical columns by 64 (32 gate rows,
-// then the 32 matching up rows; by 32 with NW = 2) so one lane holds both.  Weights are the first MFMA operand,
-// so a lane ends up with 4 consecutive columns of one row and stores them together.
-// SPLIT: grid.y cuts K into chunks of k_chunk (a multiple of 64); each writes its fp32
-// partial [M][N] to slot blockIdx.y of a.partial (SwiGLU: with NW = 2, logical columns in
-// groups of 16 gate and 16 up).
-// SHORT: K of at most 256 with one row of tiles: all of it is requested at once and multiplied after one
-// wait, because the pipeline's start and end (a wait and a barrier per 64 of K, steps over zeros)
-// are a tenth of such a call: 1, 2 and 16 rows of 512 x 256 2.65 / 3.4 / 3.6 us against 3.1 / 3.9 / 4.0,
-// 1376 x 256 SwiGLU 3.7 / 3.9 / 3.8 against 4.2 / 4.4 / 4.2.  (As a branch of the same kernel it made K = 688 0.3 us
+// Row-major activations are staged as 8 rows x 128 bytes per DMA (whole cache lines), with the eight
+// 16-byte chunks of row r stored in the order chunk ^ (r / 2 % 8), so that the 16 lanes of a fragment
+// read touch 16 different 16-byte columns of LDS; packed activations are 1 KB tiles in operand order
+// already.  SwiGLU groups logical columns by 64 (32 gate rows, then the 32 matching up rows; by 32
+// with NW = 2) so one lane holds both.  Weights are the first MFMA operand, so a lane ends up with 4
+// consecutive columns of one row and stores them together.
+// SPLIT: grid.y cuts K into chunks of
+// k_chunk (a multiple of 64); each writes its fp32 partial [M][N] to slot blockIdx.y of a.partial
+// (SwiGLU: with NW = 2, logical columns in groups of 16 gate and 16 up).
+// SHORT: K of at most 256 with
+// one row of tiles: all of it is requested at once and multiplied after one wait, because the
+// pipeline's start and end (a wait and a barrier per 64 of K, steps over zeros) are a tenth of such a
+// call: 1, 2 and 16 rows of 512 x 256 2.65 / 3.4 / 3.6 us against 3.1 / 3.9 / 4.0, 1376 x 256 SwiGLU
+// 3.7 / 3.9 / 3.8 against 4.2 / 4.4 / 4.2.  (As a branch of the same kernel it made K = 688 0.3 us
 // slower; from 33 rows on it gains nothing.)
 template <int TM, int NW, int R, int EPI, bool SPLIT, int WV, int OCC, int CACHE, bool SHORT>
 __global__ __launch_bounds__(64 * WV, OCC) void gemm_wide_kernel(GemmArgs a) {
