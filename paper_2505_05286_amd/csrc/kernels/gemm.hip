@@ -196,8 +196,8 @@ hipError_t pack_weight_launch(const uint16_t* W, int N, int K, uint16_t* out, hi
 //    Partials outgrow the array of the allocation-free entry point only where they buy much (a
 //    million outputs or more, pieces of 2048 of K), so that the shapes it serves do not hang on small
 //    gains.
-// SwiGLU of a width that is no multiple of 32 has no 64-column form (2 gate and 2 up
-//    tiles): 32 columns per wavefront at any row count.
+// SwiGLU of a width that is no multiple of 32 has no 64-column form (2 gate and 2 up tiles): 32
+// columns per wavefront at any row count.
 GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu) {
   GemmPlan p;
   const int row_tiles = (M + 15) / 16;

@@ -50,12 +50,11 @@ namespace {
 // already.  SwiGLU groups logical columns by 64 (32 gate rows, then the 32 matching up rows; by 32
 // with NW = 2) so one lane holds both.  Weights are the first MFMA operand, so a lane ends up with 4
 // consecutive columns of one row and stores them together.
-// SPLIT: grid.y cuts K into chunks of
-// k_chunk (a multiple of 64); each writes its fp32 partial [M][N] to slot blockIdx.y of a.partial
-// (SwiGLU: with NW = 2, logical columns in groups of 16 gate and 16 up).
-// SHORT: K of at most 256 with
-// one row of tiles: all of it is requested at once and multiplied after one wait, because the
-// pipeline's start and end (a wait and a barrier per 64 of K, steps over zeros) are a tenth of such a
+// SPLIT: grid.y cuts K into chunks of k_chunk (a multiple of 64); each writes its fp32 partial
+// [M][N] to slot blockIdx.y of a.partial (SwiGLU: with NW = 2, logical columns in groups of 16 gate
+// and 16 up).
+// SHORT: K of at most 256 with one row of tiles: all of it is requested at once and multiplied
+// after one wait, because the pipeline's start and end (a wait and a barrier per 64 of K, steps over zeros) are a tenth of such a
 // call: 1, 2 and 16 rows of 512 x 256 2.65 / 3.4 / 3.6 us against 3.1 / 3.9 / 4.0, 1376 x 256 SwiGLU
 // 3.7 / 3.9 / 3.8 against 4.2 / 4.4 / 4.2.  (As a branch of the same kernel it made K = 688 0.3 us
 // slower; from 33 rows on it gains nothing.)
