@@ -322,5 +322,9 @@ print("given back")
 def test_a_large_plan_is_given_back(which):
     """The thread's plans are kept between calls up to 4 MiB only (the plan of 400,000 sequences takes
     over 70 MiB)."""
-    r = subprocess.run([sys.executable, "-c", _LARGE, which], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    env = dict(os.environ)
+    if "ASAN_OPTIONS" in env:   # freed memory goes back at once there too
+        env["ASAN_OPTIONS"] += ":quarantine_size_mb=0:thread_local_quarantine_size_kb=0"
+    r = subprocess.run([sys.executable, "-c", _LARGE, which], cwd=ROOT, env=env, capture_output=True, text=True,
+                       timeout=120)
     assert r.returncode == 0 and "given back" in r.stdout, (r.returncode, r.stderr[-2000:])
