@@ -173,8 +173,8 @@ hipError_t pack_weight_launch(const uint16_t* W, int N, int K, uint16_t* out, hi
 }
 
 // Tile and split-K choice.  It depends on M through its 16-row tiles, and on M itself where the
-// partials may outgrow the allocation-free array (a million outputs): the fewer rows of a tile never
-// have larger partials than its sixteen.
+// partials fill or may outgrow the allocation-free array: the last row count of a tile (a multiple of
+// 16) or the one before has the tile's largest partials.
 //  - Up to 128 rows one row of tiles covers M and the weights' bytes are the bound, so the chip must
 //    be full: 128 columns per workgroup and K cut into the most pieces that stay within one workgroup
 //    per CU and >= 512 of K each, and shorten the pipeline; outputs of more than 256 such tiles take
@@ -244,7 +244,8 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu) {
   auto consider_splits = [&](int tm, int nw) {
     for (int s = 1; s <= most && (s == 1 || K / s >= 512); ++s)
       if (s == 1 || (nw == 4 && K / s >= 2048 && (int64_t)M * N >= 1 << 20) ||
-          (int64_t)s * row_tiles * 16 * N * 4 <= kNoallocPartials)
+          ((int64_t)s * row_tiles * 16 * N * 4 <= kNoallocPartials &&
+           (nw == 4 || (int64_t)s * M * N * 4 < kNoallocPartials)))   // (256 x 4096 x 14336 stays refused there)
         consider(tm, nw, 4, s);
   };
   if (!pairs_only) {

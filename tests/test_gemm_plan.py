@@ -5,7 +5,7 @@ import pytest
 from paper_2505_05286_amd import hxf
 
 
-@pytest.mark.parametrize("N,K,rows", [(4096, 14336, (176, 192, 208, 240, 256, 513, 600, 704, 768, 900, 1024)),
+@pytest.mark.parametrize("N,K,rows", [(4096, 14336, (176, 192, 208, 240, 251, 255, 513, 600, 704, 768, 900, 1024)),
                                       (5120, 27648, (176, 192, 513, 600, 704, 768, 900))])
 def test_down_projections_above_128_rows_take_128_columns(N, K, rows):
     """A few thousand columns and long K: 256-column workgroups leave most of the chip idle
@@ -16,12 +16,13 @@ def test_down_projections_above_128_rows_take_128_columns(N, K, rows):
 
 
 @pytest.mark.parametrize("N", [256, 688, 2048, 4096, 5120, 7168, 10240, 16383])
-def test_partials_are_largest_at_the_last_row_of_a_row_tile(N):
-    """Buffers for every row count are sized at the multiples of 16 alone; above 512 rows K is whole."""
+def test_partials_are_largest_at_the_last_rows_of_a_row_tile(N):
+    """Buffers for every row count are sized at the multiples of 16 and the rows before them alone;
+    above 512 rows K is whole."""
     for K in (512, 2048, 4096, 8192, 11008, 14336, 28672):
         for M16 in range(16, 513, 16):
-            full = hxf.op_gemm_workspace_bytes(M16, N, K)
-            assert all(hxf.op_gemm_workspace_bytes(M, N, K) <= full for M in (M16 - 15, M16 - 8, M16 - 1))
+            full = max(hxf.op_gemm_workspace_bytes(M, N, K) for M in (M16 - 1, M16))
+            assert all(hxf.op_gemm_workspace_bytes(M, N, K) <= full for M in range(M16 - 15, M16 - 1))
         assert hxf.op_gemm_workspace_bytes(513, N, K) == hxf.op_gemm_workspace_bytes(2080, N, K) == 0
 
 
@@ -40,3 +41,11 @@ def test_few_rows_cut_k_only_where_a_piece_runs_fewer_trips(N, K, pieces):
     for M in (1, 17, 64, 128):
         *_, s, k = hxf.op_gemm_plan(M, N, K, hxf.EPI_BF16)
         assert s == pieces and k % 64 == 0 and (s - 1) * k < K <= s * k, (M, s, k)
+
+
+def test_the_allocation_free_call_serves_what_it_served():
+    """Down projections whose partials the allocation-free entry point took, and one it refuses."""
+    limit = hxf.GEMM_NOALLOC_MAX_BYTES
+    assert all(hxf.op_gemm_workspace_bytes(M, 4096, 4096) <= limit for M in range(1, 513))
+    assert all(hxf.op_gemm_workspace_bytes(M, N, K) <= limit for M in range(1, 129) for N, K in ((4096, 14336), (8192, 28672)))
+    assert hxf.op_gemm_workspace_bytes(256, 4096, 14336) > limit
