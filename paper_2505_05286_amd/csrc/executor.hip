@@ -94,7 +94,7 @@ WsPlan plan_workspace(const hxf_model_cfg& m, const hxf_sched_cfg& s) {
   for (int64_t M16 = 16; M16 < std::min<int64_t>(512, p.t_max) + 16; M16 += 16)
     for (int64_t M : {M16 - 1, M16})
       for (auto& sh : shapes) {
-        GemmPlan g = gemm_plan((int)M, (int)sh[0], (int)sh[1], kMaxSplits, sh[2] != 0);
+        GemmPlan g = gemm_plan((int)M, (int)sh[0], (int)sh[1], kMaxSplits, sh[2] != 0, true);
         if (g.splits > 1) part = std::max(part, (int64_t)g.splits * M * sh[0] * 4);
       }
   int64_t o = 0;
@@ -261,7 +261,7 @@ int HipExecutor::gemm(const uint16_t* A, int lda, const uint16_t* B, const uint1
   a.lda = lda;
   a.ldc = ldc;
   a.kt = (K + 31) / 32;
-  GemmPlan p = gemm_plan(M, N, K, kMaxSplits, epi == EPI_SWIGLU);
+  GemmPlan p = gemm_plan(M, N, K, kMaxSplits, epi == EPI_SWIGLU, true);
   if (p.splits > 1 && (int64_t)p.splits * M * N * 4 > plan_.part_bytes) {
     err = "gemm: split-K partial buffer too small";
     return HXF_EINVAL;

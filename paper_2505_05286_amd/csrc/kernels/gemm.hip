@@ -198,7 +198,7 @@ hipError_t pack_weight_launch(const uint16_t* W, int N, int K, uint16_t* out, hi
 //    gains.
 // SwiGLU of a width that is no multiple of 32 has no 64-column form (2 gate and 2 up tiles): 32
 // columns per wavefront at any row count.
-GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu) {
+GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu, bool own_partials) {
   GemmPlan p;
   const int row_tiles = (M + 15) / 16;
   const bool pairs_only = swiglu && N % 64 != 0;
@@ -245,7 +245,7 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu) {
     for (int s = 1; s <= most && (s == 1 || K / s >= 512); ++s)
       if (s == 1 || (nw == 4 && K / s >= 2048 && (int64_t)M * N >= 1 << 20) ||
           ((int64_t)s * row_tiles * 16 * N * 4 <= kNoallocPartials &&
-           (nw == 4 || (int64_t)s * M * N * 4 < kNoallocPartials)))   // (256 x 4096 x 14336 stays refused there)
+           (nw == 4 || own_partials || (int64_t)s * M * N * 4 < kNoallocPartials)))   // (256 x 4096 x 14336 stays refused there)
         consider(tm, nw, 4, s);
   };
   if (!pairs_only) {

@@ -58,8 +58,9 @@ struct GemmPlan {
   int k_chunk = 0;
 };
 
-// swiglu: the plan is for the SwiGLU epilogue (N = 2F logical columns)
-GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu = false);
+// swiglu: the plan is for the SwiGLU epilogue (N = 2F logical columns); own_partials: the caller has
+// its own array for them, so nothing hangs on the size of the allocation-free one
+GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu = false, bool own_partials = false);
 // With reduce == false a split-K plan leaves its fp32 partials [splits][M][N] in
 // a.partial for the consumer to sum (no reduction launch).  e0 / e1 (may be null):
 // events recorded at the first kernel's start and the last kernel's end.
