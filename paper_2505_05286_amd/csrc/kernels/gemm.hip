@@ -142,10 +142,10 @@ struct TileCost {
   double issue0, issue1, power0, power1, fetch[4], start, tb_s_once, tb_s, part_us;
 };
 constexpr TileCost kCols64{0.136, 0.0304, 0.0665, 0.0475, {0, 0.385, 0.337, 0.312}, 1.1, 5.4, 4.1, 0.42};
+constexpr TileCost kCols64Split{0.154, 0.0308, 0.0468, 0.0448, {0, 0.364, 0.377, 0.3585}, 0.92, 9.4, 5.24, 0.505};
 constexpr TileCost kCols32{0.0816, 0.0222, 0.0245, 0.0204, {0.0714, 0.207, 0.164, 0.102}, 1.02, 5.0, 4.61, 0.592};
 
-double wide_time(int M, int N, int K, int tm, int nw, int wv, int k_chunk) {
-  const TileCost& c = nw == 2 ? kCols32 : kCols64;
+double wide_time(const TileCost& c, int M, int N, int K, int tm, int nw, int wv, int k_chunk) {
   const int tiles_m = (M + 16 * tm - 1) / (16 * tm), tiles_n = (N + 16 * nw * wv - 1) / (16 * nw * wv);
   const int splits = (K + k_chunk - 1) / k_chunk;
   const int wgs = tiles_m * tiles_n * splits;
@@ -229,9 +229,9 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu, bool own_pa
   }
   const int most = M <= 512 && N < 16384 && !swiglu ? max_splits : 1;
   double best = 0;
-  auto consider = [&](int tm, int nw, int wv, int s) {
+  auto consider = [&](const TileCost& cost, int tm, int nw, int wv, int s) {
     const int kc = ((K + s - 1) / s + 63) / 64 * 64;
-    const double t = wide_time(M, N, K, tm, nw, wv, kc);
+    const double t = wide_time(cost, M, N, K, tm, nw, wv, kc);
     if (best != 0 && t >= best) return;
     best = t;
     p.tm = tm;
@@ -246,18 +246,30 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu, bool own_pa
       if (s == 1 || (nw == 4 && K / s >= 2048 && (int64_t)M * N >= 1 << 20) ||
           ((int64_t)s * row_tiles * 16 * N * 4 <= kNoallocPartials &&
            (nw == 4 || own_partials || (int64_t)s * M * N * 4 < kNoallocPartials)))   // (256 x 4096 x 14336 stays refused there)
-        consider(tm, nw, 4, s);
+        consider(nw == 2 ? kCols32 : kCols64, tm, nw, 4, s);
   };
+  auto height = [&](int tm) { return row_tiles > tm || (tm % 2 == 0 && row_tiles + 2 > tm); };   // one row of tiles: the next even height
   if (!pairs_only) {
     for (int tm = 4; tm <= 16; ++tm)
-      if (row_tiles > tm || (tm % 2 == 0 && row_tiles + 2 > tm)) consider_splits(tm, 4);   // one row of tiles: the next even height
+      if (height(tm)) consider_splits(tm, 4);
     // (measured at 129-512 rows too: it wins only where two rows of 144 fit just so, 288 rows of
     // 55296 x 5120 155 us against 174, and is even or slower elsewhere)
-    if (M > 512) consider(9, 4, 8, 1);
+    if (M > 512) consider(kCols64, 9, 4, 8, 1);
   }
   if (!swiglu || pairs_only)
     for (int tm = 3; tm <= 12; ++tm)
       if (row_tiles + 1 > tm) consider_splits(tm, 2);   // one row of tiles: the height itself
+  if (p.splits > 1 && (int64_t)p.splits * M * N * 4 > kNoallocPartials) {
+    // The allocation-free entry point refuses this plan whatever its tile: chosen again among those it
+    // refuses, by constants fitted up to 512 rows (5120 x 27648 at 251 rows in six pieces 93 us, in the
+    // five of the first choice 100; 4096 x 14336 at 256 in seven 50, in five 52).
+    best = 0;
+    for (int tm = 4; tm <= 16; ++tm)
+      for (int s = 2; height(tm) && s <= most && K / s >= 2048; ++s) {
+        const int kc = ((K + s - 1) / s + 63) / 64 * 64;
+        if ((int64_t)((K + kc - 1) / kc) * row_tiles * 16 * N * 4 > kNoallocPartials) consider(kCols64Split, tm, 4, 4, s);
+      }
+  }
   return p;
 }
 

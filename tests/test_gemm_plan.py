@@ -49,3 +49,11 @@ def test_the_allocation_free_call_serves_what_it_served():
     assert all(hxf.op_gemm_workspace_bytes(M, 4096, 4096) <= limit for M in range(1, 513))
     assert all(hxf.op_gemm_workspace_bytes(M, N, K) <= limit for M in range(1, 129) for N, K in ((4096, 14336), (8192, 28672)))
     assert hxf.op_gemm_workspace_bytes(256, 4096, 14336) > limit
+
+
+@pytest.mark.parametrize("M,N,K,pieces", [(208, 5120, 27648, 6), (251, 5120, 27648, 6), (256, 4096, 14336, 7),
+                                          (144, 8192, 28672, 8), (256, 10240, 8192, 3)])
+def test_plans_beyond_the_allocation_free_array_take_the_pieces_that_measured_best(M, N, K, pieces):
+    """Within 4% of the best split of the sweep (251 x 5120 x 27648: six pieces 93 us, five 100)."""
+    assert hxf.op_gemm_plan(M, N, K, hxf.EPI_RESID)[4] == pieces
+    assert hxf.op_gemm_workspace_bytes(M, N, K) > hxf.GEMM_NOALLOC_MAX_BYTES
