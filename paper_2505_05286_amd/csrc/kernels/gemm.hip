@@ -213,16 +213,20 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu, bool own_pa
     int s = 1;
     if (p.nw == 2)
       while (s + 1 <= max_splits && tiles * (s + 1) <= 256 && K / (s + 1) >= 512) ++s;
-    // The pipeline runs 1 + 8 n steps of 32 of K, and one or two steps left over singly, which wait
-    // for all their loads and cost about a trip of eight: a cut that saves no trip only adds partials
-    // (one row of 6144 x 4096 in five pieces 13.6 us, in four 13.2; 64 rows 18.7 and 18.0; 5120 x
-    // 5120 in six and five 14.2 and 13.8, 64 rows 20.1 and 18.9; of 40 such shapes measured the worst
-    // loses 2%).
-    auto steps = [&](int pieces) {
+    // Of up to that many pieces, those that cost least: the pipeline runs 1 + 8 n steps of 32 of K,
+    // and one or two steps left over singly, which wait for all their loads and cost about a trip of
+    // eight; every piece adds its partials (us per step by row tiles and per MB, fitted to 2,690
+    // launches of 100 shapes at 1-128 rows: 0.35% slower than the best split on average, 7% at
+    // worst).  One row of 6144 x 4096 in five pieces 13.6 us, in four 13.2; 64 rows 18.7 and 18.0;
+    // 5120 x 5120 in six and five 14.2 and 13.8; 128 rows of 4096 x 4096 in eight and four 23.8 and
+    // 21.0.
+    auto cost = [&](int pieces) {
       const int n = std::min(((K + pieces - 1) / pieces + 63) / 64 * 2, (K + 31) / 32), trips = (n + 4) / 8;
-      return 1 + 8 * trips + 8 * std::max(n - 1 - 8 * trips, 0);
+      return (0.03 + 0.01 * p.tm) * (1 + 8 * trips + 8 * std::max(n - 1 - 8 * trips, 0)) +
+             (pieces > 1 ? 0.33e-6 * pieces * row_tiles * 16 * (double)N * 4 : 0.0);
     };
-    while (s > 1 && steps(s - 1) <= steps(s)) --s;
+    for (int n = s - 1; n >= 1; --n)
+      if (cost(n) <= cost(s)) s = n;
     p.k_chunk = ((K + s - 1) / s + 63) / 64 * 64;
     p.splits = (K + p.k_chunk - 1) / p.k_chunk;
     return p;

@@ -35,12 +35,13 @@ def test_wide_outputs_take_128_columns_where_256_leave_the_cus_uneven(N, last):
             assert hxf.op_gemm_plan(M, N, K, hxf.EPI_F32)[1] == (2 if M <= last else 4), M
 
 
-@pytest.mark.parametrize("N,K,pieces", [(6144, 4096, 4), (5120, 5120, 5), (6144, 3072, 4), (4096, 14336, 8), (7168, 5120, 4),
-                                        (4096, 4096, 8), (2048, 8192, 8), (256, 688, 1)])
-def test_few_rows_cut_k_only_where_a_piece_runs_fewer_trips(N, K, pieces):
-    for M in (1, 17, 64, 128):
+@pytest.mark.parametrize("N,K,pieces", [(6144, 4096, (4, 4, 4, 4)), (5120, 5120, (5, 5, 5, 5)), (4096, 4096, (8, 8, 4, 4)),
+                                        (4096, 14336, (8, 8, 8, 8)), (7168, 5120, (4, 4, 4, 4)),
+                                        (2048, 8192, (8, 8, 8, 8)), (256, 688, (1, 1, 1, 1))])
+def test_few_rows_cut_k_only_where_a_piece_saves_more_than_its_partials(N, K, pieces):
+    for M, want in zip((1, 17, 64, 128), pieces):
         *_, s, k = hxf.op_gemm_plan(M, N, K, hxf.EPI_BF16)
-        assert s == pieces and k % 64 == 0 and (s - 1) * k < K <= s * k, (M, s, k)
+        assert s == want and k % 64 == 0 and (s - 1) * k < K <= s * k, (M, s, k)
 
 
 def test_the_allocation_free_call_serves_what_it_served():
