@@ -142,7 +142,7 @@ struct TileCost {
   double issue0, issue1, power0, power1, fetch[4], start, tb_s_once, tb_s, part_us;
 };
 constexpr TileCost kCols64{0.136, 0.0304, 0.0665, 0.0475, {0, 0.385, 0.337, 0.312}, 1.1, 5.4, 4.1, 0.42};
-constexpr TileCost kCols64Split{0.154, 0.0308, 0.0468, 0.0448, {0, 0.364, 0.377, 0.3585}, 0.92, 9.4, 5.24, 0.505};
+constexpr TileCost kCols64Split{0.058, 0.0378, 0.0349, 0.0406, {0, 0.4206, 0.408, 0.3654}, 0.847, 8.73, 4.39, 0.585};
 constexpr TileCost kCols32{0.0816, 0.0222, 0.0245, 0.0204, {0.0714, 0.207, 0.164, 0.102}, 1.02, 5.0, 4.61, 0.592};
 
 double wide_time(const TileCost& c, int M, int N, int K, int tm, int nw, int wv, int k_chunk) {
