@@ -252,7 +252,10 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu, bool own_pa
            (nw == 4 || own_partials || (int64_t)s * M * N * 4 < kNoallocPartials)))   // (256 x 4096 x 14336 stays refused there)
         consider(nw == 2 ? kCols32 : kCols64, tm, nw, 4, s);
   };
-  auto height = [&](int tm) { return row_tiles > tm || (tm % 2 == 0 && row_tiles + 2 > tm); };   // one row of tiles: the next even height
+  // heights worth an estimate: the lowest for its rows of tiles (a higher one only costs more), and for
+  // one row of 64-column tiles the next even one
+  auto lowest = [&](int tm, int first) { return tm == first || (row_tiles + tm - 1) / tm < (row_tiles + tm - 2) / (tm - 1); };
+  auto height = [&](int tm) { return row_tiles > tm ? lowest(tm, 4) : tm % 2 == 0 && row_tiles + 2 > tm; };
   if (!pairs_only) {
     for (int tm = 4; tm <= 16; ++tm)
       if (height(tm)) consider_splits(tm, 4);
@@ -262,7 +265,7 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits, bool swiglu, bool own_pa
   }
   if (!swiglu || pairs_only)
     for (int tm = 3; tm <= 12; ++tm)
-      if (row_tiles + 1 > tm) consider_splits(tm, 2);   // one row of tiles: the height itself
+      if (row_tiles + 1 > tm && lowest(tm, 3)) consider_splits(tm, 2);   // one row of tiles: the height itself
   if (p.splits > 1 && (int64_t)p.splits * M * N * 4 > kNoallocPartials) {
     // The allocation-free entry point refuses this plan whatever its tile: chosen again among those it
     // refuses, by constants fitted up to 512 rows (5120 x 27648 at 251 rows in six pieces 93 us, in the
